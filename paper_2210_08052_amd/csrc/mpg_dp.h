@@ -7,14 +7,13 @@
 #include "mpg_internal.h"
 #include "mpg_walk.h"
 
-// Occupancy targets of the DP kernels (waves per SIMD; 1 = no cap).  The
-// score-only kernels of width <= 2 run four waves per SIMD (128 VGPRs; 3.4%
-// faster than three waves on the 10k batch); the width-2 traceback kernels
-// run three (4.9% on the traceback batch), which their LDS also caps.  Width 1
-// with traceback and width 4 keep the registers they need (about 320 and 400
-// with traceback: one wave per SIMD; width 4 at two waves slows the long-tail
-// batch 279 -> 343 ms: its long pairs' strip pipelines are the critical path,
-// and a second wave halves each strip's own pace).
+// Occupancy targets of the DP kernels (waves per SIMD; 1 = no cap).  An fp32
+// subtraction issues beside another wavefront's max, so more wavefronts pair
+// more of them (cycles per instruction of an even mix: 3.0 at three waves per
+// SIMD, 2.5 at four, 2.35 at eight).  Score-only kernels of width <= 2 and
+// width 1 with traceback run four (128 VGPRs, 10,240 B of LDS each); width 2
+// with traceback three, which its LDS caps; width 4 keeps the registers it
+// needs.
 #ifndef MPG_SCORE_WAVES
 #define MPG_SCORE_WAVES 4
 #endif
@@ -23,13 +22,15 @@
 #endif
 // A scheduling barrier between the steps of a chunk keeps each step's
 // instructions together (bounding the registers the unrolled chunk needs):
-// kept in the score-only kernels, left out of the traceback ones, which run
-// 2% faster with neighbouring steps interleaved (timed on the 10k batch).
-#ifndef MPG_STEP_BARRIER
-#define MPG_STEP_BARRIER 1
-#endif
-#ifndef MPG_TB_STEP_BARRIER
-#define MPG_TB_STEP_BARRIER 0
+// kept in the integer score-only kernels, left out of the traceback ones (2%
+// faster with neighbouring steps interleaved, 10k batch) and of the fp32 ones
+// (10k batch 10.43 -> 10.32 ms, rescoring 3,000 pairs 1.62 -> 1.59 ms).
+template <bool TB, bool F32>
+struct StepBarrier {
+    static constexpr bool value = !TB && !F32;
+};
+#ifndef MPG_TB1_WAVES
+#define MPG_TB1_WAVES 4
 #endif
 #ifndef MPG_K4_WAVES
 #define MPG_K4_WAVES 1
@@ -37,7 +38,7 @@
 template <int K, bool TB>
 struct WavesPerEu {
     static constexpr int value =
-        K > 2 ? MPG_K4_WAVES : (TB ? (K == 2 ? MPG_TB_WAVES : 1) : MPG_SCORE_WAVES);
+        K > 2 ? MPG_K4_WAVES : (TB ? (K == 2 ? MPG_TB_WAVES : MPG_TB1_WAVES) : MPG_SCORE_WAVES);
 };
 
 namespace mpg {
@@ -45,7 +46,6 @@ namespace dev {
 
 
 constexpr int kShr1 = 0x138;  // DPP wave_shr:1
-constexpr int kShl1 = 0x130;  // DPP wave_shl:1
 
 static __constant__ uint8_t kAaOfLetter[26] = {0,  20, 4,  3,  6,  13, 7,  8,  9,  22, 11, 10, 12,
                                         2,  22, 14, 5,  1,  15, 16, 22, 19, 17, 22, 18, 21};
@@ -73,29 +73,6 @@ __device__ __forceinline__ int imax3(int a, int b, int c) { return imax(imax(a, 
 __device__ __forceinline__ int shr1(int old, int v) {
     return __builtin_amdgcn_update_dpp(old, v, kShr1, 0xF, 0xF, false);
 }
-__device__ __forceinline__ int shl1(int old, int v) {
-    return __builtin_amdgcn_update_dpp(old, v, kShl1, 0xF, 0xF, false);
-}
-
-// max(x of lane - 1, v) with the lane shift as the max's own operand (one
-// instruction instead of a move and a max); lane 0 keeps `old`.  The s_nop
-// gives the two wait states a DPP read needs after a VALU write of x.
-__device__ __forceinline__ int max_from_left(int old, int x, int v) {
-    int r = old;
-    asm("s_nop 1\n\tv_max_i32_dpp %0, %1, %2 wave_shr:1 row_mask:0xf bank_mask:0xf"
-        : "+v"(r)
-        : "v"(x), "v"(v));
-    return r;
-}
-// (x of lane - 1) - v, likewise; lane 0 keeps `old`
-__device__ __forceinline__ int sub_from_left(int old, int x, int v) {
-    int r = old;
-    asm("s_nop 1\n\tv_sub_u32_dpp %0, %1, %2 wave_shr:1 row_mask:0xf bank_mask:0xf"
-        : "+v"(r)
-        : "v"(x), "v"(v));
-    return r;
-}
-
 __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
@@ -177,26 +154,118 @@ __device__ __forceinline__ int wave_find_owner(const int64_t* __restrict__ start
 template <int K, bool TB, bool SEG = false>
 struct LdsLayout {
     static constexpr int DS = 16;              // descriptor bytes per row
-    static constexpr int PS = TB ? 2 : 1;      // profile entry bytes
+    static constexpr int PS = TB ? 2 : 1;      // profile score bytes
+    static constexpr int PE = K * PS;          // a lane's scores for one amino acid
+    static constexpr int PB = PE < 4 ? 4 : PE; // a lane's block of a profile row
+    static constexpr int PN = PB / PE;         // amino acids of one row
     static constexpr int SW = 64 * K;          // strip width
     static constexpr int RING = 128 * DS;      // two chunks of descriptors
-    static constexpr int PROF = 25 * SW * PS;  // profile: 24 aa + poison row
+    static constexpr int PROF = (25 + PN - 1) / PN * 64 * PB;  // 24 aa + poison row
     static constexpr int IN = 64 * 8;          // incoming boundary of the chunk
-    // outgoing boundary, then the other lanes' dummy slots (one per lane and
-    // step at width 2, one per lane otherwise)
-    static constexpr int OUT = (K == 2 ? 192 : 128) * 8;
+    // outgoing boundary (64 rows), then the slots through which each lane
+    // hands its last column to the lane on its right (one per lane and step)
+    static constexpr int OUT = 192 * 8;
     static constexpr int MAT = 640;            // substitution matrix, then the letter codes
     static constexpr int RING2 = RING + PROF + IN + OUT + MAT;  // SEG: second ring
     static constexpr int WAVE = RING2 + (SEG ? RING : 0);
 };
 
-// Sentinels per layout.  The floor modes keep -infinity small enough that a
-// shifted end-tracking key of any sentinel-derived value stays negative.
-template <int MODE, bool TB>
+// The profile in LDS: a lane's scores of one amino acid for its K columns lie
+// together, in a block of at least 4 bytes of its own, so that the 64 lanes,
+// each with the amino acid of its own row, read 64 different banks.  (Rows of
+// 64 one-byte scores put four lanes on a bank and several amino acids on the
+// same one.)  The row descriptors hold the byte offset of their amino acid
+// within lane 0's block, for the pair's own width and kind.  Each column is
+// one read and one add: both columns in one read need sub-dword operands
+// (SDWA), whose instructions, like DPP, issue beside no other wavefront's
+// (10k batch 11.5 -> 13.3 ms).
+__host__ __device__ __forceinline__ int prof_offset(int K, bool tb, int tr) {
+    const int pe = K * (tb ? 2 : 1);
+    if (pe >= 4) return tr * 64 * pe;
+    return pe == 2 ? (tr >> 1) * 256 + (tr & 1) * 2 : (tr >> 2) * 256 + (tr & 3);
+}
+
+// How a value v (in score-only units, or the 16x units of the traceback
+// layout) is held in a 32-bit register.
+//
+// F32 = false: the integer v itself.
+//
+// F32 = true: the bits of the fp32 number BIAS + v, an exact integer in
+// [2^23, 2^24), where neighbouring integers are neighbouring bit patterns: a
+// 32-bit integer add to the bits (the substitution score) is the same sum,
+// the low bits are the integer's own (the winner nibble), and integer max and
+// compare of the bits order the numbers.  Penalties are subtracted with
+// v_sub_f32, exactly.  The point: on gfx950 an fp32 add or subtract issues
+// beside another wavefront's v_max / v_max3 / v_alignbit, an integer add or
+// subtract does not.  Measured per SIMD at four wavefronts, alternating the
+// two kinds: 2.5 cycles per instruction with v_sub_f32 and v_max3_i32, 4.5
+// with v_sub_u32; about half of a cell's instructions are subtractions.
+// The planner (f32_ok) proves that every reachable value fits; other pairs
+// run the integer form.  Values below BIAS in LOCAL mode (never on a path)
+// and the sentinel (2^22, or 2^21 without a floor) lie below 2^23 and stay
+// positive numbers, so the order of the bits still holds.
+//
+// The floor modes keep -infinity small enough that a shifted end-tracking key
+// of any sentinel-derived value stays below every reachable cell's.
+template <int MODE, bool TB, bool F32 = false>
 struct Sentinel {
-    static constexpr int NEG = floor_mode(MODE) ? (TB ? -(1 << 29) : -(1 << 25)) : -(1 << 30);
-    static constexpr int UNREACH = floor_mode(MODE) ? NEG / 2 : -(1 << 29);
+    static constexpr bool LOC = MODE == MPG_LOCAL;
+    static constexpr int NEG = F32 ? (LOC ? kF32NegLocal : kF32Neg)
+                                   : (floor_mode(MODE) ? (TB ? -(1 << 29) : -(1 << 25)) : -(1 << 30));
+    static constexpr int UNREACH = F32 ? kF32Unreach : (floor_mode(MODE) ? NEG / 2 : -(1 << 29));
+    static constexpr int ZERO = F32 ? (LOC ? kF32ZeroLocal : kF32Zero) : 0;  // the value 0
+    // the score of a reachable H
+    static __device__ __forceinline__ int score(int h) { return (h - ZERO) >> (TB ? 4 : 0); }
 };
+
+template <bool F32>
+__device__ __forceinline__ int vsub(int a, int b) {
+    return F32 ? __float_as_int(__int_as_float(a) - __int_as_float(b)) : a - b;
+}
+template <bool F32>
+__device__ __forceinline__ int vadd(int a, int b) {
+    return F32 ? __float_as_int(__int_as_float(a) + __int_as_float(b)) : a + b;
+}
+// A per-lane penalty in the register form (the uniform ones come in DevParams).
+template <bool F32>
+__device__ __forceinline__ int vnum(int v) {
+    return F32 ? __float_as_int((float)v) : v;
+}
+// End-tracking keys of a chunk: the cell's H above, 63 - step in the low 6
+// bits, so that one max keeps the first best cell.  F32: compared unsigned;
+// the bits of H shifted out at the top are the same for every value an H can
+// take (exponents of 2^21 to 2^24).
+// The keys of two consecutive steps enter one three-input max: an even step
+// leaves its key in kp, the odd one takes both (64 steps: none is left over).
+template <bool TB, bool F32>
+__device__ __forceinline__ void key_push(int& bk, int& kp, int h, int t) {
+    const int k = (int)(((uint32_t)h << (TB ? 2 : 6)) | (uint32_t)(63 - t));
+    if (!F32) {
+        bk = k > bk ? k : bk;
+        return;
+    }
+    if (t & 1) {
+        const uint32_t q = (uint32_t)kp > (uint32_t)k ? (uint32_t)kp : (uint32_t)k;
+        bk = (int)(q > (uint32_t)bk ? q : (uint32_t)bk);
+        // kept in this step: left free, the compiler takes the maxima of a
+        // chunk's 64 keys at its end and spills every step's H until then
+        asm volatile("" : "+v"(bk));
+    } else {
+        kp = k;
+        asm volatile("" : "+v"(kp));
+    }
+}
+template <bool TB, bool F32>
+__device__ __forceinline__ int key_value(int bk) {
+    if (F32)
+        return TB ? (int)((((uint32_t)bk >> 6) << 4) | 0x40000000u)
+                  : (int)(((uint32_t)bk >> 6) | 0x48000000u);
+    return TB ? (bk >> 6) << 4 : bk >> 6;
+}
+template <bool F32>
+__host__ __device__ constexpr int key_none() {
+    return F32 ? 0 : INT_MIN;
+}
 
 // a + b + k in one instruction (left to itself, the compiler shares b + k
 // between a lane's columns and spends two)
@@ -214,6 +283,16 @@ __device__ __forceinline__ int add3k(int a, int b) {
 // other (planner's score bound), so the difference never overflows.
 __device__ __forceinline__ uint32_t push_open(uint32_t acc, int diff) {
     return __builtin_amdgcn_alignbit(acc, (uint32_t)diff, 31);
+}
+
+// Issue priority of a wavefront whose strip runs `nchunks` of at most `most`
+// chunks of the launch: 3 from half of the longest on, 0 below an eighth.
+// The scale is the longest pair's (items[0] in a batch).
+__device__ __forceinline__ void strip_priority(int nchunks, int most) {
+    if (2 * nchunks >= most) __builtin_amdgcn_s_setprio(3);
+    else if (4 * nchunks >= most) __builtin_amdgcn_s_setprio(2);
+    else if (8 * nchunks >= most) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
 }
 
 // Per-pair state shared by the waves that work on the pair's strips.
@@ -312,15 +391,15 @@ __device__ __forceinline__ void local_record(mpg_dev_result& R, const PairJob& J
 // [0, split), pair B's in [split, 64); both strips run the same number of
 // chunks.  Each lane works on its own pair's rows (the segment's lane k at
 // step s on row s - k), reads its pair's descriptors from that pair's LDS
-// ring and takes its left neighbour's H and I by the same DPP shift as a
-// whole-wave strip; the first lane of each segment takes them from its pair's
-// incoming boundary instead (one select per value and step).  A pair of one
+// ring and takes its left neighbour's H and I through the same LDS slots as a
+// whole-wave strip; the first lane of each segment reads its pair's incoming
+// boundary instead, by its own address.  A pair of one
 // strip starts from the -infinity column; otherwise its previous strip
 // streams the boundary through HBM as for any strip.  With traceback (batch
 // calls, walked afterwards by the walk kernel) each lane stores its direction
 // bits into its own pair's block of the strip at its lane within the
 // segment: the layout of a whole-wave strip.
-template <int K, bool TB, bool NOI, bool NOF>
+template <int K, bool TB, bool NOI, bool NOF, bool F32>
 __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restrict__ jobs,
                                          PairState* __restrict__ pst, int* __restrict__ prog_g,
                                          const uint8_t* __restrict__ prot,
@@ -329,8 +408,15 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
                                          const DevParams& P, uint8_t* smem, const int8_t* smat,
                                          const uint8_t* saa) {
     using LY = LdsLayout<K, TB, true>;
-    constexpr int NEG = Sentinel<MPG_LOCAL, TB>::NEG;
-    constexpr int UNREACH = Sentinel<MPG_LOCAL, TB>::UNREACH;
+    using SV = Sentinel<MPG_LOCAL, TB, F32>;
+    constexpr int NEG = SV::NEG;
+    constexpr int UNREACH = SV::UNREACH;
+    // F32 traceback: the carried donor fields include the nibble difference of
+    // the state that reads them (one add per row; the integer form adds it in
+    // the three-input add that opens the state)
+    constexpr bool DDN = F32 && TB;
+    constexpr int kOne = F32 ? 0x3F800000 : 1, kTwo = F32 ? 0x40000000 : 2;
+    constexpr int kNone = key_none<F32>();
     const int lane = threadIdx.x & 63;
     const int code = -1 - item.y;
     const int ja = item.x, jb = code >> 6, split = code & 63;
@@ -359,14 +445,16 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
     uint8_t* ringA = smem;
     uint8_t* ringB = smem + LY::RING2;
     uint8_t* prof = smem + LY::RING;
+    const uint8_t* const prof_l = prof + lane * LY::PB;
     int2* inbA = (int2*)(smem + LY::RING + LY::PROF);
     int2* inbB = (int2*)(smem + LY::RING + LY::PROF + LY::IN);
     // penalties in the layout of the variant (as in the whole-wave strips)
-    const int cq = TB ? 16 * (P.q + P.e) - 13 : P.q;
-    const int cqD = TB ? 16 * (P.q + P.e) - 12 : P.q;
-    const int ce = TB ? 16 * P.e : P.e;
-    const int cf = TB ? 16 * P.f : P.f;
-    int cf11 = cf - 11, cf9 = cf - 9;
+    const int cq = P.pen[F32][TB][kPenI];
+    const int cqD = P.pen[F32][TB][kPenD];
+    const int ce = P.pen[F32][TB][kPenExt];
+    const int cf = P.pen[F32][TB][kPenFs];
+    int cf11 = P.pen[F32][TB][kPenF1];
+    int cf9 = P.pen[F32][TB][kPenG1];
     asm volatile("" : "+s"(cf11), "+s"(cf9));
     const int2 neg2 = make_int2(NEG, NEG);
 
@@ -387,15 +475,13 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
         for (int tr = 0; tr < 25; ++tr) {
             const bool poison = pc < 0 || tr == 24;
             const int v = tr < 24 ? sv[tr < 24 ? tr : 0] : 0;
-            if (TB)
-                ((int16_t*)prof)[(c * 25 + tr) * 64 + lane] =
-                    (int16_t)(poison ? -32768 : 16 * v + 14);
-            else
-                ((int8_t*)prof)[(c * 25 + tr) * 64 + lane] = (int8_t)(poison ? -128 : v);
+            uint8_t* at = prof + prof_offset(K, TB, tr) + lane * LY::PB + c * LY::PS;
+            if (TB) *(int16_t*)at = (int16_t)(poison ? -32768 : 16 * v + 14);
+            else *(int8_t*)at = (int8_t)(poison ? -128 : v);
         }
     }
     int h1[K], h2[K], h3[K], d1[K], d2[K], d3[K], a1[K], b1[K], c1[K];
-    int best[K], bstep[K], bk[K], fp[K];
+    int best[K], bstep[K], bk[K], kp[K], fp[K];
     uint32_t nacc[K], xacc[5][K];
 #pragma unroll
     for (int c = 0; c < K; ++c) {
@@ -404,8 +490,8 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
         a1[c] = b1[c] = c1[c] = NEG;
         best[c] = NEG;
         bstep[c] = 0;
-        bk[c] = INT_MIN;
-        fp[c] = TB ? NEG - cf11 : NEG - cf;
+        bk[c] = kp[c] = kNone;
+        fp[c] = TB ? vsub<F32>(NEG, cf11) : vsub<F32>(NEG, cf);
         nacc[c] = 0;
 #pragma unroll
         for (int x = 0; x < 5; ++x) xacc[x][c] = 0;
@@ -416,7 +502,9 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
     {
         const int4 u = *(const int4*)(dsc_l + (int64_t)(-kk - 1 + kDescLo) * LY::DS);
         const int4 v = *(const int4*)(dsc_l + (int64_t)(-kk - 2 + kDescLo) * LY::DS);
-        dd0 = u.z; aam1 = u.w; ddm1 = v.z; aam2 = v.w;
+        aam1 = u.w; aam2 = v.w;
+        dd0 = DDN ? vadd<F32>(u.z, kOne) : u.z;
+        ddm1 = DDN ? vadd<F32>(v.z, kTwo) : v.z;
     }
     // both rings: rows -64..-1 then 0..63 of each pair
     {
@@ -445,16 +533,20 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
         seenB = ld_dev(&progB[stripB - 1]);
     }
     int4 pfA = make_int4(0, 0, 0, 0), pfB = make_int4(0, 0, 0, 0);
-    // this lane's ring and incoming rows; at width 2 as one LDS offset each,
-    // opaque to the compiler: a select of the two pairs' areas is distributed
-    // over the steps' addresses, which are invariant across chunks, and the
-    // compiler hoists all of them into registers, which width 2 spills (the
-    // widths that run one wave per SIMD hold them; see the outgoing rows)
+    // this lane's ring, the slot it hands its last column through, and where
+    // it finds its left neighbour's (step t: row t of its pair's incoming
+    // boundary, or the slot that lane wrote one step before), as LDS offsets
+    // opaque to the compiler: it would distribute the selects over the steps'
+    // addresses, which are invariant across chunks, and hoist all of them
+    // into registers
     int ring_off = sg ? LY::RING2 : 0;
-    int inb_off = sg ? LY::RING + LY::PROF + LY::IN : LY::RING + LY::PROF;
-    if constexpr (K == 2) asm volatile("" : "+v"(ring_off), "+v"(inb_off));
-    const uint8_t* ring_l = K != 2 ? (sg ? ringB : ringA) : smem + ring_off;
-    const int2* inb_l = K != 2 ? (sg ? inbB : inbA) : (const int2*)(smem + inb_off);
+    int out_off = LY::RING + LY::PROF + LY::IN + (64 + lane) * 8;
+    int in_off = first ? (sg ? LY::RING + LY::PROF + LY::IN : LY::RING + LY::PROF)
+                       : LY::RING + LY::PROF + LY::IN + (62 + lane) * 8;
+    asm volatile("" : "+v"(ring_off), "+v"(in_off), "+v"(out_off));
+    const uint8_t* ring_l = smem + ring_off;
+    const int2* in_l = (const int2*)(smem + in_off);
+    int2* out_l = (int2*)(smem + out_off);
 
     for (int ch = 0; ch < nchunks && !failed; ++ch) {
         // incoming boundary rows ch*64 .. ch*64+63 of each pair with a left strip
@@ -496,45 +588,30 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
         pfB = *(const int4*)(dscB + (int64_t)((ch + 1) * 64 + lane + kDescLo) * LY::DS);
         const uint8_t* rb = ring_l + (64 - kk) * LY::DS;
         auto ld_prof = [&](const int4& x0, int* scv) {
-            if (TB) {
-                const int16_t* pr = (const int16_t*)prof + x0.x * 64 + lane;
+            const uint8_t* pr = prof_l + x0.x;
 #pragma unroll
-                for (int c = 0; c < K; ++c) scv[c] = pr[c * 25 * 64];
-            } else {
-                const int8_t* pr = (const int8_t*)prof + x0.x * 64 + lane;
-#pragma unroll
-                for (int c = 0; c < K; ++c) scv[c] = pr[c * 25 * 64];
-            }
+            for (int c = 0; c < K; ++c)
+                scv[c] = TB ? (int)*(const int16_t*)(pr + c * LY::PS)
+                            : (int)*(const int8_t*)(pr + c * LY::PS);
         };
         uint8_t* tbblk = TB ? tb_l + (int64_t)ch * (kTbBlockBytes * K) : nullptr;
         int4 cd0 = *(const int4*)(rb), nd0 = *(const int4*)(rb + LY::DS);
         int csc[K];
         ld_prof(cd0, csc);
-        int2 cin = inb_l[0];
+        // step 0: the neighbour's last step of the chunk before
+        // (shifted in every lane, then selected: a shift reads nothing from a
+        // lane that a branch has masked off)
+        const int hs = shr1(NEG, Hout), is = shr1(NEG, Iout);
+        const int2 in0 = in_l[0];
+        int2 cin = make_int2(first ? in0.x : hs, first ? in0.y : is);
 #pragma unroll
         for (int t = 0; t < 64; ++t) {
             int4 fd0 = make_int4(0, 0, 0, 0);
             if (t + 2 < 64) fd0 = *(const int4*)(rb + (t + 2) * LY::DS);
             int nsc[K];
-            int2 nin = make_int2(0, 0);
-            if (t + 1 < 64) {
-                ld_prof(nd0, nsc);
-                nin = inb_l[t + 1];
-            }
+            if (t + 1 < 64) ld_prof(nd0, nsc);
             const int4 ds0 = cd0;
-            // a segment's first lane takes its own pair's boundary (the
-            // shift's own lane 0 value is replaced too, so the shift needs no
-            // copy of the boundary value as its old operand)
-            int hl0, il0;
-            if constexpr (K == 2) {
-                hl0 = __builtin_amdgcn_mov_dpp(Hout, kShr1, 0xF, 0xF, true);
-                il0 = __builtin_amdgcn_mov_dpp(Iout, kShr1, 0xF, 0xF, true);
-            } else {
-                hl0 = shr1(cin.x, Hout);
-                il0 = shr1(cin.y, Iout);
-            }
-            hl0 = first ? cin.x : hl0;
-            il0 = first ? cin.y : il0;
+            const int hl0 = cin.x, il0 = cin.y;
             const int z = ds0.y;
             int Hn[K], In[K], Dn[K], An[K], Bn[K], Cn[K];
 #pragma unroll
@@ -544,23 +621,23 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
                 const int L1 = c ? h1[c - 1] : hl1;
                 const int L3 = c ? h3[c - 1] : hl3;
                 if (!TB) {
-                    const int D = imax(h3[c] - cq, d3[c]) - ce;
-                    const int I = imax(L0 - cq, IL) - ce;
+                    const int D = vsub<F32>(imax(vsub<F32>(h3[c], cq), d3[c]), ce);
+                    const int I = vsub<F32>(imax(vsub<F32>(L0, cq), IL), ce);
                     const int M = L3 + csc[c];
                     int pf = 0;
                     if (!NOF) {
-                        pf = imax(L1, h1[c]) - cf;
+                        pf = vsub<F32>(imax(L1, h1[c]), cf);
                         asm("" : "+v"(pf));
                     }
                     int H;
                     if (!NOI) {
-                        const int A = imax(h1[c] - ddm1, a1[c]);
-                        const int B = imax(L1 - dd0, b1[c]);
-                        const int C = imax(L1 - ds0.z, c1[c]);
+                        const int A = imax(vsub<F32>(h1[c], ddm1), a1[c]);
+                        const int B = imax(vsub<F32>(L1, dd0), b1[c]);
+                        const int C = imax(vsub<F32>(L1, ds0.z), c1[c]);
                         An[c] = A; Bn[c] = B; Cn[c] = C;
-                        const int x = imax3(D, A - ds0.w, B - aam2);
-                        if (!NOF) H = imax3(x, imax3(C - aam1, pf, fp[c]), imax3(M, I, z));
-                        else H = imax3(x, imax3(C - aam1, M, I), z);
+                        const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
+                        if (!NOF) H = imax3(x, imax3(vsub<F32>(C, aam1), pf, fp[c]), imax3(M, I, z));
+                        else H = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
                     } else {
                         if (!NOF) H = imax(imax3(D, pf, fp[c]), imax3(M, I, z));
                         else H = imax(imax3(D, M, I), z);
@@ -568,37 +645,37 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
                     if (!NOF) fp[c] = pf;
                     Hn[c] = H; In[c] = I; Dn[c] = D;
                 } else {
-                    const int oD = h3[c] - cqD, xD = d3[c] - ce;
-                    xacc[1][c] = push_open(xacc[1][c], xD - oD);
+                    const int oD = vsub<F32>(h3[c], cqD), xD = vsub<F32>(d3[c], ce);
+                    xacc[1][c] = push_open(xacc[1][c], vsub<F32>(xD, oD));
                     int D = imax(oD, xD);
-                    const int oI = L0 - cq, xI = IL - ce;
-                    xacc[0][c] = push_open(xacc[0][c], xI - oI);
+                    const int oI = vsub<F32>(L0, cq), xI = vsub<F32>(IL, ce);
+                    xacc[0][c] = push_open(xacc[0][c], vsub<F32>(xI, oI));
                     int I = imax(oI, xI);
                     const int M = L3 + csc[c];
                     int p1 = 0, p2 = 0;
                     if (!NOF) {
-                        p1 = imax(L1 - cf11, h1[c] - cf9);
+                        p1 = imax(vsub<F32>(L1, cf11), vsub<F32>(h1[c], cf9));
                         asm("" : "+v"(p1));
-                        p2 = fp[c] - 1;
+                        p2 = vsub<F32>(fp[c], kOne);
                         fp[c] = p1;
                     }
                     asm("" : "+v"(D), "+v"(I));
                     int Hk;
                     if (!NOI) {
-                        const int oA = add3k<2>(h1[c], ddm1);
-                        xacc[2][c] = push_open(xacc[2][c], a1[c] - oA);
+                        const int oA = DDN ? vadd<F32>(h1[c], ddm1) : add3k<2>(h1[c], ddm1);
+                        xacc[2][c] = push_open(xacc[2][c], vsub<F32>(a1[c], oA));
                         int A = imax(oA, a1[c]);
-                        const int oB = add3k<1>(L1, dd0);
-                        xacc[3][c] = push_open(xacc[3][c], b1[c] - oB);
+                        const int oB = DDN ? vadd<F32>(L1, dd0) : add3k<1>(L1, dd0);
+                        xacc[3][c] = push_open(xacc[3][c], vsub<F32>(b1[c], oB));
                         int B = imax(oB, b1[c]);
-                        const int oC = L1 + ds0.z;
-                        xacc[4][c] = push_open(xacc[4][c], c1[c] - oC);
+                        const int oC = vadd<F32>(L1, ds0.z);
+                        xacc[4][c] = push_open(xacc[4][c], vsub<F32>(c1[c], oC));
                         int C = imax(oC, c1[c]);
                         asm("" : "+v"(A), "+v"(B), "+v"(C));
                         An[c] = A; Bn[c] = B; Cn[c] = C;
-                        const int x = imax3(D, A - ds0.w, B - aam2);
-                        if (!NOF) Hk = imax3(x, imax3(C - aam1, p1, p2), imax3(M, I, z));
-                        else Hk = imax3(x, imax3(C - aam1, M, I), z);
+                        const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
+                        if (!NOF) Hk = imax3(x, imax3(vsub<F32>(C, aam1), p1, p2), imax3(M, I, z));
+                        else Hk = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
                     } else {
                         if (!NOF) Hk = imax(imax3(D, p1, p2), imax3(M, I, z));
                         else Hk = imax(imax3(D, M, I), z);
@@ -610,7 +687,7 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
             }
 #pragma unroll
             for (int c = 0; c < K; ++c)
-                bk[c] = imax(bk[c], (Hn[c] << (TB ? 2 : 6)) | (63 - t));
+                key_push<TB, F32>(bk[c], kp[c], Hn[c], t);
             if (TB && (t & 7) == 7) {
 #pragma unroll
                 for (int c = 0; c < K; ++c)
@@ -633,22 +710,24 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
                 d3[c] = d2[c]; d2[c] = d1[c]; d1[c] = Dn[c];
                 if (!NOI) { a1[c] = An[c]; b1[c] = Bn[c]; c1[c] = Cn[c]; }
             }
-            ddm1 = dd0; dd0 = ds0.z; aam2 = aam1; aam1 = ds0.w;
+            ddm1 = DDN ? vadd<F32>(dd0, kOne) : dd0;
+            dd0 = DDN ? vadd<F32>(ds0.z, kOne) : ds0.z;
+            aam2 = aam1; aam1 = ds0.w;
             Hout = Hn[K - 1];
             Iout = In[K - 1];
             cd0 = nd0; nd0 = fd0;
 #pragma unroll
             for (int c = 0; c < K; ++c) csc[c] = nsc[c];
-            cin = nin;
-            if (TB ? MPG_TB_STEP_BARRIER : MPG_STEP_BARRIER) __builtin_amdgcn_sched_barrier(0);
+            out_l[t] = make_int2(Hout, Iout);
+            if (t + 1 < 64) cin = in_l[t + 1];
+            if (StepBarrier<TB, F32>::value) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int c = 0; c < K; ++c) {
-            int v = bk[c] >> 6;
+            const int v = key_value<TB, F32>(bk[c]);
             const int tt = 63 - (bk[c] & 63);
-            if (TB) v <<= 4;  // back to 16*H units
             if (v > best[c]) { best[c] = v; bstep[c] = ch * 64 + tt; }
-            bk[c] = INT_MIN;
+            bk[c] = kNone;
         }
     }
 
@@ -658,7 +737,7 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
     for (int c = 0; c < K; ++c) {
         const int row = bstep[c] - kk, col = col0 + c;
         if (col <= m_l && row >= 0 && row <= n_l && best[c] > UNREACH) {
-            const uint64_t k2 = end_key(TB ? (best[c] >> 4) : best[c], row, col);
+            const uint64_t k2 = end_key(SV::score(best[c]), row, col);
             key = k2 > key ? k2 : key;
         }
     }
@@ -704,7 +783,7 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
 // to items taken earlier by running wavefronts, so the waits always end.
 // PRO: the query is a position-specific profile block (prof_scores /
 // prof_gaps) instead of protein letters and one matrix.
-template <int K, int MODE, bool TB, bool NOI, bool NOF, bool PRO>
+template <int K, int MODE, bool TB, bool NOI, bool NOF, bool PRO, bool F32>
 __global__ void __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(WavesPerEu<K, TB>::value)))
 dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int nitems,
@@ -718,31 +797,37 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
     // the mixed variant runs EXTEND and fixed-end pairs (per-pair modes)
     constexpr bool MIXED = MODE == kModeMixed;
     constexpr int SM = MIXED ? (int)MPG_GLOBAL : MODE;  // mode of the sentinels and the floor
-    constexpr int NEG = Sentinel<SM, TB>::NEG;
-    constexpr int UNREACH = Sentinel<SM, TB>::UNREACH;
+    using SV = Sentinel<SM, TB, F32>;
+    constexpr int NEG = SV::NEG;
+    constexpr int UNREACH = SV::UNREACH;
+    // F32 traceback: the carried donor fields include the nibble difference of
+    // the state that reads them (one add per row; the integer form adds it in
+    // the three-input add that opens the state)
+    constexpr bool DDN = F32 && TB;
+    constexpr int kOne = F32 ? 0x3F800000 : 1, kTwo = F32 ? 0x40000000 : 2;
+    constexpr int kNone = key_none<F32>();
     constexpr int ZN = TB ? 15 : 0;  // nibble of the start candidate
-    // The first column's I term takes the left lane's I as a DPP operand of
-    // the max (score-only) or subtraction (traceback) that consumes it.
-    // Timed on the 10k batch: 3% faster at one column per lane, 1% with
-    // traceback, not faster in the score-only kernels of wider lanes.
-    constexpr bool FUSE_I = TB || K == 1;
     extern __shared__ __align__(16) uint8_t smem[];
     const int lane = threadIdx.x & 63;
     uint8_t* ring = smem;
     uint8_t* prof = smem + LY::RING;
+    const uint8_t* const prof_l = prof + lane * LY::PB;
     int2* inb = (int2*)(smem + LY::RING + LY::PROF);
     int2* outb = (int2*)(smem + LY::RING + LY::PROF + LY::IN);
-    // step t's outgoing row: lane 63 writes slot t, lane l < 63 a dummy slot,
-    // never read.  A per-step select of the slot is invariant across chunks,
-    // and the compiler hoists all 64 of them into registers.  Width 2 (three
-    // or four waves per SIMD) spills them, and every reload waited for the
-    // chunk's direction-bit stores, so it writes slot 64 + l + t through one
-    // base per lane with the step in the store's immediate offset (traceback
-    // batch DP 26.3 -> 25.4 ms with the packed strips' offsets below).  The
-    // other widths keep the select: built without the hoisted registers they
-    // run more waves per SIMD, which slows the long-tail batch (280 -> 331 ms)
-    // and doubles the serving latency (p50 1.9 -> 3.9 ms).
-    int2* const outw = outb + (lane == 63 ? 0 : 64 + lane);
+    // A lane hands its last column's H and I to the lane on its right through
+    // LDS: lane l < 63 writes slot 64 + l + t at step t, the next lane reads
+    // that slot for step t + 1 (LDS operations of a wavefront run in order),
+    // and lane 0 reads row t + 1 of the incoming boundary with the same
+    // instruction.  Lane 63 writes the outgoing boundary, slot t.  A shift by
+    // DPP takes two instructions that issue beside no other wavefront's, and
+    // a select in packed strips; this read takes the place of the broadcast
+    // read of the boundary row, and the step's other terms cover its latency.
+    // One base per lane, the step in the immediate offset.
+    int out_off = LY::RING + LY::PROF + LY::IN + (lane == 63 ? 0 : 64 + lane) * 8;
+    int in_off = lane ? LY::RING + LY::PROF + LY::IN + (62 + lane) * 8 : LY::RING + LY::PROF;
+    asm volatile("" : "+v"(in_off), "+v"(out_off));
+    const int2* const in_l = (const int2*)(smem + in_off);
+    int2* const out_l = (int2*)(smem + out_off);
     int8_t* smat = (int8_t*)(smem + LY::RING + LY::PROF + LY::IN + LY::OUT);
     uint8_t* saa = (uint8_t*)(smat + 24 * 24);
     // the matrix and the letter codes, read with per-lane indices when a
@@ -758,16 +843,18 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
     };
 
     // penalties in the layout of this variant
-    const int cq = TB ? 16 * (P.q + P.e) - 13 : P.q;   // I open  (TB: nibble 13)
-    const int cqD = TB ? 16 * (P.q + P.e) - 12 : P.q;  // D open  (TB: nibble 12)
-    const int ce = TB ? 16 * P.e : P.e;
-    const int cf = TB ? 16 * P.f : P.f;
+    const int cq = P.pen[F32][TB][kPenI];   // I open  (TB: nibble 13)
+    const int cqD = P.pen[F32][TB][kPenD];  // D open  (TB: nibble 12)
+    const int ce = P.pen[F32][TB][kPenExt];
+    const int cf = P.pen[F32][TB][kPenFs];
     // traceback: the F1 and G1 candidates' offsets (16f less their nibbles),
     // kept opaque so that the compiler does not share H - 16f between them
     // and add each nibble with a separate instruction
-    int cf11 = cf - 11, cf9 = cf - 9;
+    int cf11 = P.pen[F32][TB][kPenF1];
+    int cf9 = P.pen[F32][TB][kPenG1];
     asm volatile("" : "+s"(cf11), "+s"(cf9));
 
+    const int most = jobs[items[0].x].nchunks;
     // Items are taken when the previous one is done (claiming ahead would
     // hold a strip that the next strip of its pair then waits for).
     for (;;) {
@@ -779,9 +866,10 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
         const int it = __builtin_amdgcn_readfirstlane(atomicAdd(qhead, lane == 0 ? 1 : 0));
         if (it >= nitems) break;
         const int2 item = items[it];
+        strip_priority(jobs[item.x].nchunks, most);
         if constexpr (SEGOK) {
             if (item.y < 0) {
-                seg_item<K, TB, NOI, NOF>(item, jobs, pst, prog_g, prot, desc, bnd, tbbuf, sink,
+                seg_item<K, TB, NOI, NOF, F32>(item, jobs, pst, prog_g, prot, desc, bnd, tbbuf, sink,
                                           P, smem, smat, saa);
                 continue;
             }
@@ -820,13 +908,9 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                 for (int tr = 0; tr < 25; ++tr) {
                     const bool poison = pc < 0 || tr == 24;
                     const int v = tr < 24 ? sv[tr < 24 ? tr : 0] : 0;
-                    // column c of every lane in a row of its own, so that each
-                    // step reads one sign-extended entry per column
-                    if (TB)
-                        ((int16_t*)prof)[(c * 25 + tr) * 64 + lane] =
-                            (int16_t)(poison ? -32768 : 16 * v + 14);
-                    else
-                        ((int8_t*)prof)[(c * 25 + tr) * 64 + lane] = (int8_t)(poison ? -128 : v);
+                    uint8_t* at = prof + prof_offset(K, TB, tr) + lane * LY::PB + c * LY::PS;
+                    if (TB) *(int16_t*)at = (int16_t)(poison ? -32768 : 16 * v + 14);
+                    else *(int8_t*)at = (int8_t)(poison ? -128 : v);
                 }
             }
         }
@@ -839,10 +923,10 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
             if (PRO) {
                 const int16_t* g = prof_gaps(Pa, m) + 4 * imin(col0 + c, m);
                 const int oi = g[0], ei = g[1], od = g[2], ed = g[3];
-                cqv[c] = TB ? 16 * (oi + ei) - 13 : oi;
-                cev[c] = TB ? 16 * ei : ei;
-                cqDv[c] = TB ? 16 * (od + ed) - 12 : od;
-                ceDv[c] = TB ? 16 * ed : ed;
+                cqv[c] = vnum<F32>(TB ? 16 * (oi + ei) - 13 : oi);
+                cev[c] = vnum<F32>(TB ? 16 * ei : ei);
+                cqDv[c] = vnum<F32>(TB ? 16 * (od + ed) - 12 : od);
+                ceDv[c] = vnum<F32>(TB ? 16 * ed : ed);
             } else {
                 cqv[c] = cq;
                 cev[c] = ce;
@@ -850,20 +934,9 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                 ceDv[c] = ce;
             }
         }
-        // With FUSE_I the incoming boundary rows are kept with their I part
-        // pre-combined for the first column of the strip, as lane 0 needs it
-        // (the other lanes take the same terms from their left neighbour
-        // within the step): score-only max(H - q, I), traceback I less the
-        // extension.
-        const int cq0 = __builtin_amdgcn_readfirstlane(cqv[0]);
-        const int ce0 = __builtin_amdgcn_readfirstlane(cev[0]);
-        auto in_row = [&](int2 w) {
-            if (!FUSE_I) return w;
-            return make_int2(w.x, TB ? w.y - ce0 : imax(w.x - cq0, w.y));
-        };
-        if (act) inb[lane] = in_row(make_int2(NEG, NEG));
+        if (act) inb[lane] = make_int2(NEG, NEG);
         int h1[K], h2[K], h3[K], d1[K], d2[K], d3[K], a1[K], b1[K], c1[K];
-        int zl[K], best[K], bstep[K], bk[K], bkt[K], hn[K];
+        int zl[K], best[K], bstep[K], bk[K], bkt[K], hn[K], kp[K];
         int fp[K];  // previous row's frameshift term (F1/G1 maximum)
         uint32_t nacc[K];
         uint32_t xacc[5][K];  // extension decisions of the last steps, per lane
@@ -878,15 +951,15 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
             h1[c] = h2[c] = h3[c] = NEG;
             d1[c] = d2[c] = d3[c] = NEG;
             a1[c] = b1[c] = c1[c] = NEG;
-            zl[c] = floor0 ? INT_MAX : ((col0 + c == 0) ? ZN : NEG + ZN);
+            zl[c] = floor0 ? INT_MAX : ((col0 + c == 0) ? SV::ZERO + ZN : NEG + ZN);
             best[c] = NEG;
             bstep[c] = 0;
-            bk[c] = INT_MIN;
+            bk[c] = kp[c] = kNone;
             bkt[c] = 0;
             hn[c] = NEG;
             // the frameshift term of the row above the strip's first (every
             // H there is -infinity)
-            fp[c] = TB ? NEG - cf11 : NEG - cf;
+            fp[c] = TB ? vsub<F32>(NEG, cf11) : vsub<F32>(NEG, cf);
             nacc[c] = 0;
 #pragma unroll
             for (int x = 0; x < 5; ++x) xacc[x][c] = 0;
@@ -899,7 +972,9 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
         if (act) {
             const int4 u = *(const int4*)(dsc_g + (int64_t)(-lane - 1 + kDescLo) * LY::DS);
             const int4 v = *(const int4*)(dsc_g + (int64_t)(-lane - 2 + kDescLo) * LY::DS);
-            dd0 = u.z; aam1 = u.w; ddm1 = v.z; aam2 = v.w;
+            aam1 = u.w; aam2 = v.w;
+        dd0 = DDN ? vadd<F32>(u.z, kOne) : u.z;
+        ddm1 = DDN ? vadd<F32>(v.z, kTwo) : v.z;
         }
         // descriptor ring: rows -64..-1 then 0..63
         int4 pf0 = make_int4(0, 0, 0, 0);
@@ -931,7 +1006,7 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                 // garbage-row values or were never written: -infinity)
                 const bool beyond = ch * 64 + lane > n;
                 if (from_left) {
-                    inb[lane] = in_row(beyond ? make_int2(NEG, NEG) : nb);
+                    inb[lane] = beyond ? make_int2(NEG, NEG) : nb;
                     if (ch + 1 < nchunks) {
                         const int need = ch + 3 < nchunks ? ch + 3 : nchunks;
                         if (__builtin_amdgcn_readfirstlane(seen) < need &&
@@ -958,22 +1033,20 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                 // profile entries and the incoming boundary value one step ahead.
                 auto ld_desc = [&](int tt, int4& x0) { x0 = *(const int4*)(rb + tt * LY::DS); };
                 auto ld_prof = [&](const int4& x0, int* scv) {
-                    if (TB) {
-                        const int16_t* pr = (const int16_t*)prof + x0.x * 64 + lane;
+                    const uint8_t* pr = prof_l + x0.x;
 #pragma unroll
-                        for (int c = 0; c < K; ++c) scv[c] = pr[c * 25 * 64];
-                    } else {
-                        const int8_t* pr = (const int8_t*)prof + x0.x * 64 + lane;
-#pragma unroll
-                        for (int c = 0; c < K; ++c) scv[c] = pr[c * 25 * 64];
-                    }
+                    for (int c = 0; c < K; ++c)
+                        scv[c] = TB ? (int)*(const int16_t*)(pr + c * LY::PS)
+                                    : (int)*(const int8_t*)(pr + c * LY::PS);
                 };
                 int4 cd0, nd0;
                 ld_desc(0, cd0);
                 ld_desc(1, nd0);
                 int csc[K];
                 ld_prof(cd0, csc);
-                int2 cin = inb[0];
+                // step 0: the neighbour's last step of the chunk before
+                const int2 in0 = inb[0];
+                int2 cin = make_int2(shr1(in0.x, Hout), shr1(in0.y, Iout));
 
 #pragma unroll
                 for (int t = 0; t < 64; ++t) {
@@ -981,14 +1054,9 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                     int4 fd0 = make_int4(0, 0, 0, 0);
                     if (t + 2 < 64) ld_desc(t + 2, fd0);
                     int nsc[K];
-                    int2 nin = make_int2(0, 0);
-                    if (t + 1 < 64) {
-                        ld_prof(nd0, nsc);
-                        nin = inb[t + 1];
-                    }
+                    if (t + 1 < 64) ld_prof(nd0, nsc);
                     const int4 ds0 = cd0;
-                    const int hl0 = shr1(cin.x, Hout);
-                    const int il0 = FUSE_I ? 0 : shr1(cin.y, Iout);
+                    const int hl0 = cin.x, il0 = cin.y;
                     const int zr = ds0.y;
                     int Hn[K], In[K], Dn[K], An[K], Bn[K], Cn[K];
 #pragma unroll
@@ -1000,32 +1068,31 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                         const int L3 = c ? h3[c - 1] : hl3;
                         const int z = floor_mode(SM) ? zr : imin(zr, zl[c]);
                         if (!TB) {
-                            const int D = imax(h3[c] - cqDv[c], d3[c]) - ceDv[c];
+                            const int D = vsub<F32>(imax(vsub<F32>(h3[c], cqDv[c]), d3[c]), ceDv[c]);
                             // column 0 takes I(i, j-1) from the left lane inside
                             // the max (lane 0 from the boundary row)
-                            const int I = (c || !FUSE_I ? imax(L0 - cqv[c], IL)
-                                                        : max_from_left(cin.y, Iout, L0 - cqv[c])) -
-                                          cev[c];
+                            const int oI = vsub<F32>(L0, cqv[c]);
+                            const int I = vsub<F32>(imax(oI, IL), cev[c]);
                             const int M = L3 + csc[c];
                             // frameshifts: F1 and G1 of this row cost f each, and F2,
                             // G2 are the previous row's F1, G1 (H two rows up is the
                             // history one row up), so one max per cell covers all four
                             int pf = 0;
                             if (!NOF) {
-                                pf = imax(L1, h1[c]) - cf;
+                                pf = vsub<F32>(imax(L1, h1[c]), cf);
                                 // opaque to the next row: the compiler would otherwise
                                 // expand fp - ... back into four candidates there
                                 asm("" : "+v"(pf));
                             }
                             int H;
                             if (!NOI) {
-                                const int A = imax(h1[c] - ddm1, a1[c]);
-                                const int B = imax(L1 - dd0, b1[c]);
-                                const int C = imax(L1 - ds0.z, c1[c]);
+                                const int A = imax(vsub<F32>(h1[c], ddm1), a1[c]);
+                                const int B = imax(vsub<F32>(L1, dd0), b1[c]);
+                                const int C = imax(vsub<F32>(L1, ds0.z), c1[c]);
                                 An[c] = A; Bn[c] = B; Cn[c] = C;
-                                const int x = imax3(D, A - ds0.w, B - aam2);
-                                if (!NOF) H = imax3(x, imax3(C - aam1, pf, fp[c]), imax3(M, I, z));
-                                else H = imax3(x, imax3(C - aam1, M, I), z);
+                                const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
+                                if (!NOF) H = imax3(x, imax3(vsub<F32>(C, aam1), pf, fp[c]), imax3(M, I, z));
+                                else H = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
                             } else {
                                 if (!NOF) H = imax(imax3(D, pf, fp[c]), imax3(M, I, z));
                                 else H = imax(imax3(D, M, I), z);
@@ -1033,13 +1100,12 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                             if (!NOF) fp[c] = pf;
                             Hn[c] = H; In[c] = I; Dn[c] = D;
                         } else {
-                            const int oD = h3[c] - cqDv[c], xD = d3[c] - ceDv[c];
-                            xacc[1][c] = push_open(xacc[1][c], xD - oD);
+                            const int oD = vsub<F32>(h3[c], cqDv[c]), xD = vsub<F32>(d3[c], ceDv[c]);
+                            xacc[1][c] = push_open(xacc[1][c], vsub<F32>(xD, oD));
                             int D = imax(oD, xD);
-                            const int oI = L0 - cqv[c];
-                            const int xI = c || !FUSE_I ? IL - cev[c]
-                                                        : sub_from_left(cin.y, Iout, cev[c]);
-                            xacc[0][c] = push_open(xacc[0][c], xI - oI);
+                            const int oI = vsub<F32>(L0, cqv[c]);
+                            const int xI = vsub<F32>(IL, cev[c]);
+                            xacc[0][c] = push_open(xacc[0][c], vsub<F32>(xI, oI));
                             int I = imax(oI, xI);
                             const int M = L3 + csc[c];
                             // F1 (nibble 11) and G1 (9) of this row; F2 (10) and G2
@@ -1047,11 +1113,11 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                             // maximum is the previous row's maximum less one
                             int p1 = 0, p2 = 0;
                             if (!NOF) {
-                                p1 = imax(L1 - cf11, h1[c] - cf9);
+                                p1 = imax(vsub<F32>(L1, cf11), vsub<F32>(h1[c], cf9));
                                 // opaque to the next row: the compiler would otherwise
                                 // expand fp - 1 back into four candidates there
                                 asm("" : "+v"(p1));
-                                p2 = fp[c] - 1;
+                                p2 = vsub<F32>(fp[c], kOne);
                                 fp[c] = p1;
                             }
                             // the states enter H's maximum as they are: left visible,
@@ -1060,20 +1126,20 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                             asm("" : "+v"(D), "+v"(I));
                             int Hk;
                             if (!NOI) {
-                                const int oA = add3k<2>(h1[c], ddm1);
-                                xacc[2][c] = push_open(xacc[2][c], a1[c] - oA);
+                                const int oA = DDN ? vadd<F32>(h1[c], ddm1) : add3k<2>(h1[c], ddm1);
+                                xacc[2][c] = push_open(xacc[2][c], vsub<F32>(a1[c], oA));
                                 int A = imax(oA, a1[c]);
-                                const int oB = add3k<1>(L1, dd0);
-                                xacc[3][c] = push_open(xacc[3][c], b1[c] - oB);
+                                const int oB = DDN ? vadd<F32>(L1, dd0) : add3k<1>(L1, dd0);
+                                xacc[3][c] = push_open(xacc[3][c], vsub<F32>(b1[c], oB));
                                 int B = imax(oB, b1[c]);
-                                const int oC = L1 + ds0.z;
-                                xacc[4][c] = push_open(xacc[4][c], c1[c] - oC);
+                                const int oC = vadd<F32>(L1, ds0.z);
+                                xacc[4][c] = push_open(xacc[4][c], vsub<F32>(c1[c], oC));
                                 int C = imax(oC, c1[c]);
                                 asm("" : "+v"(A), "+v"(B), "+v"(C));
                                 An[c] = A; Bn[c] = B; Cn[c] = C;
-                                const int x = imax3(D, A - ds0.w, B - aam2);
-                                if (!NOF) Hk = imax3(x, imax3(C - aam1, p1, p2), imax3(M, I, z));
-                                else Hk = imax3(x, imax3(C - aam1, M, I), z);
+                                const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
+                                if (!NOF) Hk = imax3(x, imax3(vsub<F32>(C, aam1), p1, p2), imax3(M, I, z));
+                                else Hk = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
                             } else {
                                 if (!NOF) Hk = imax(imax3(D, p1, p2), imax3(M, I, z));
                                 else Hk = imax(imax3(D, M, I), z);
@@ -1109,7 +1175,7 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                     } else if (MODE == MPG_LOCAL) {
 #pragma unroll
                         for (int c = 0; c < K; ++c)
-                            bk[c] = imax(bk[c], (Hn[c] << (TB ? 2 : 6)) | (63 - t));
+                            key_push<TB, F32>(bk[c], kp[c], Hn[c], t);
                     } else {
 #pragma unroll
                         for (int c = 0; c < K; ++c) {
@@ -1144,21 +1210,18 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                         d3[c] = d2[c]; d2[c] = d1[c]; d1[c] = Dn[c];
                         if (!NOI) { a1[c] = An[c]; b1[c] = Bn[c]; c1[c] = Cn[c]; }
                     }
-                    ddm1 = dd0; dd0 = ds0.z; aam2 = aam1; aam1 = ds0.w;
+                    ddm1 = DDN ? vadd<F32>(dd0, kOne) : dd0;
+                    dd0 = DDN ? vadd<F32>(ds0.z, kOne) : ds0.z;
+                    aam2 = aam1; aam1 = ds0.w;
                     Hout = Hn[K - 1];
                     Iout = In[K - 1];
-                    // lane 63 records the row; the other lanes write to slots
-                    // of their own, so the store needs no branch (a branch
-                    // splits the step's scheduling region and costs spills)
-                    if constexpr (K == 2) outw[t] = make_int2(Hout, Iout);
-                    else outb[lane == 63 ? t : 64 + lane] = make_int2(Hout, Iout);
+                    out_l[t] = make_int2(Hout, Iout);
+                    if (t + 1 < 64) cin = in_l[t + 1];
                     // rotate the pipeline
                     cd0 = nd0; nd0 = fd0;
 #pragma unroll
                     for (int c = 0; c < K; ++c) csc[c] = nsc[c];
-                    cin = nin;
-                    if (TB ? MPG_TB_STEP_BARRIER : MPG_STEP_BARRIER)
-                        __builtin_amdgcn_sched_barrier(0);
+                    if (StepBarrier<TB, F32>::value) __builtin_amdgcn_sched_barrier(0);
                 }  // steps
 
                 // merge the chunk's best into the strip's best (first maximum)
@@ -1166,11 +1229,10 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
 #pragma unroll
                     for (int c = 0; c < K; ++c) {
                         int v, tt;
-                        if (MODE == MPG_LOCAL) { v = bk[c] >> 6; tt = 63 - (bk[c] & 63); }
+                        if (MODE == MPG_LOCAL) { v = key_value<TB, F32>(bk[c]); tt = 63 - (bk[c] & 63); }
                         else { v = bk[c]; tt = bkt[c]; }
-                        if (TB && MODE == MPG_LOCAL) v <<= 4;  // back to 16*H units
                         if (v > best[c]) { best[c] = v; bstep[c] = ch * 64 + tt; }
-                        bk[c] = INT_MIN;
+                        bk[c] = kNone;
                     }
                 }
                 // publish the strip's last column for rows ch*64-63+lane.  The
@@ -1231,7 +1293,7 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                 for (int c = 0; c < K; ++c) {
                     const int row = bstep[c] - lane;
                     const int col = col0 + c;
-                    const int v = TB ? (best[c] >> 4) : best[c];
+                    const int v = SV::score(best[c]);
                     if (col <= m && row >= 0 && row <= n && best[c] > UNREACH) {
                         const uint64_t k2 = end_key(v, row, col);
                         key = k2 > key ? k2 : key;
@@ -1287,7 +1349,7 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                     R.p_end = -1;
                 } else {
                     R.status = MPG_OK;
-                    R.score = TB ? (gv >> 4) : gv;
+                    R.score = SV::score(gv);
                     R.g_end = n;
                     R.p_end = m;
                 }
@@ -1334,7 +1396,7 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
     }  // queue
 }
 
-template <int K, int MODE, bool TB, bool PRO>
+template <int K, int MODE, bool TB, bool PRO, bool F32>
 hipError_t launch_dp_t(hipStream_t s, int ncu, const DevParams& P, const PairJob* jobs,
                        const int2* items, int nitems, int* qhead, PairState* pst, int* prog,
                        const uint8_t* prot, const uint8_t* desc, int2* bnd, uint8_t* tbbuf,
@@ -1350,11 +1412,11 @@ hipError_t launch_dp_t(hipStream_t s, int ncu, const DevParams& P, const PairJob
         static int per_cu = 0;                                                                  \
         if (per_cu <= 0 &&                                                                      \
             hipOccupancyMaxActiveBlocksPerMultiprocessor(                                       \
-                &per_cu, dp_kernel<K, MODE, TB, NI, NF, PRO>, 64, lds) != hipSuccess)           \
+                &per_cu, dp_kernel<K, MODE, TB, NI, NF, PRO, F32>, 64, lds) != hipSuccess)           \
             per_cu = 0;                                                                         \
         const int waves = per_cu > 0 ? per_cu * ncu : 8 * ncu;                                \
         dim3 g(nitems < waves ? nitems : waves);                                                \
-        hipLaunchKernelGGL((dp_kernel<K, MODE, TB, NI, NF, PRO>), g, b, lds, s, jobs, items,   \
+        hipLaunchKernelGGL((dp_kernel<K, MODE, TB, NI, NF, PRO, F32>), g, b, lds, s, jobs, items,   \
                            nitems, qhead, pst, prog, prot, desc, bnd, tbbuf, sink, P);          \
     } while (0)
     if (!noi && !nof) MPG_LAUNCH(false, false);
@@ -1365,15 +1427,15 @@ hipError_t launch_dp_t(hipStream_t s, int ncu, const DevParams& P, const PairJob
     return hipGetLastError();
 }
 
-template <int K, bool PRO>
+template <int K, bool PRO, bool F32>
 hipError_t launch_dp_k(hipStream_t s, int ncu, bool tb, const DevParams& P, const PairJob* jobs,
                        const int2* items, int nitems, int* qhead, PairState* pst, int* prog,
                        const uint8_t* prot, const uint8_t* desc, int2* bnd, uint8_t* tbbuf,
                        const DpSink& sink) {
 #define MPG_MODE(M)                                                                             \
-    return tb ? launch_dp_t<K, M, true, PRO>(s, ncu, P, jobs, items, nitems, qhead, pst, prog, \
+    return tb ? launch_dp_t<K, M, true, PRO, F32>(s, ncu, P, jobs, items, nitems, qhead, pst, prog, \
                                              prot, desc, bnd, tbbuf, sink)                      \
-              : launch_dp_t<K, M, false, PRO>(s, ncu, P, jobs, items, nitems, qhead, pst, prog, \
+              : launch_dp_t<K, M, false, PRO, F32>(s, ncu, P, jobs, items, nitems, qhead, pst, prog, \
                                               prot, desc, bnd, tbbuf, sink)
     switch (P.mode) {
         case MPG_LOCAL: MPG_MODE(MPG_LOCAL);

@@ -16,6 +16,14 @@ namespace mpg {
 constexpr int kNeg = -(1 << 30);
 constexpr int kUnreachable = -(1 << 29);  // anything below is -infinity
 
+// The fp32 form of the DP kernels' values (Sentinel in mpg_dp.h): the bits of
+// the number standing for the value 0, for -infinity, and the line between
+// reachable and unreachable.  LOCAL: 0 is 2^23, -infinity 2^22; the other
+// modes, whose values go below 0: 0 is 2^23 + 2^22, -infinity 2^21.
+constexpr int kF32ZeroLocal = 0x4B000000, kF32NegLocal = 0x4A800000;
+constexpr int kF32Zero = 0x4B400000, kF32Neg = 0x4A000000;
+constexpr int kF32Unreach = 0x4AC00000;  // 2^22 + 2^21
+
 // Row descriptor table covers rows [-kDescLo, nsteps + kDescHi).
 constexpr int kDescLo = 128;
 constexpr int kDescHi = 64;
@@ -40,7 +48,14 @@ struct DevParams {
     uint8_t donor[128];
     uint8_t acceptor[128];
     int32_t max_polls;  // polls of a bounded wait before it gives up (kMaxPolls)
+    // the penalties of the DP kernels' register forms, in the order of Pen:
+    // pen[value form: 0 integer, 1 the bits of the fp32 number][traceback]
+    int32_t pen[2][2][6];
 };
+// Penalties of a DP kernel: gap open (+ extend with traceback) of I and of D,
+// gap extend, frameshift, and (traceback) the frameshift less F1's and G1's
+// nibble.  With traceback 16x, less the nibble of the state or move.
+enum Pen { kPenI, kPenD, kPenExt, kPenFs, kPenF1, kPenG1 };
 static_assert(offsetof(DevParams, mat) % 4 == 0, "the DP kernel copies mat in dwords");
 // A strip waits for its left neighbour's progress for at most this many
 // polls (well under a second) before the pair reports MPG_E_DEVICE.
@@ -64,7 +79,7 @@ struct PairJob {
     int32_t prog_off;    // index of strip 0's progress counter
     int32_t i16;         // 1: runs in a packed int16 job (see PackJob)
     int32_t mode;        // boundary mode of this pair (MPG_LOCAL ... MPG_EXTEND_LEFT)
-    int32_t _pad;
+    int32_t f32;         // 1: values held as fp32 numbers, 0: as integers
 };
 static_assert(sizeof(PairJob) == 96, "PairJob layout");
 
@@ -129,7 +144,8 @@ hipError_t launch_prepass(hipStream_t s, const PairJob* jobs, const int64_t* row
 // and prog zeroed by launch_init.
 // pro: the pairs are position-specific queries (prot points at their
 // profile blocks; K must be 1 or 2).
-hipError_t launch_dp(hipStream_t s, int K, bool tb, bool pro, int ncu, const DevParams& P,
+// f32: the pairs' values are held as fp32 numbers (every PairJob::f32 is 1).
+hipError_t launch_dp(hipStream_t s, int K, bool tb, bool pro, bool f32, int ncu, const DevParams& P,
                      const PairJob* jobs, const int2* items, int nitems, int* qhead, void* pst,
                      int* prog, const uint8_t* prot, const uint8_t* desc, int2* bnd,
                      uint8_t* tbbuf, const DpSink& sink);

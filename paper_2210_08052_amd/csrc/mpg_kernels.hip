@@ -16,7 +16,7 @@
 //    k holding K adjacent columns.  At step s lane k computes row s-k, so the
 //    anti-diagonal order satisfies every dependency (rows i-1..i-3 of its own
 //    columns live in registers; the left neighbour's H and I of the same row
-//    arrive by a DPP wave_shr:1).  Lane 0 takes the left strip's last column
+//    arrive through a slot in LDS).  Lane 0 takes the left strip's last column
 //    from HBM, where the wavefront running the left strip publishes it 64
 //    rows at a time behind a progress counter; the kernel is persistent and
 //    takes (pair, strip) items from one queue, longest pair first;
@@ -91,7 +91,9 @@ __global__ void __launch_bounds__(256) prepass_kernel(const PairJob* __restrict_
             const int x = i0 - 4 + k;
             b[k] = (x >= 1 && x <= n) ? dna_code(T[x - 1]) : 4;
         }
-        const int neg = neg_for(J.mode, J.tb != 0);
+        const bool local = J.mode == MPG_LOCAL;
+        const int neg = J.f32 ? (local ? kF32NegLocal : kF32Neg) : neg_for(J.mode, J.tb != 0);
+        const int zero = J.f32 ? (local ? kF32ZeroLocal : kF32Zero) : 0;
         const bool floor = floor_mode(J.mode);
         const int64_t at = J.desc_off + (int64_t)(i0 + kDescLo) * 16 - s_base;
         uint8_t* rowp = s_out + at;
@@ -114,16 +116,18 @@ __global__ void __launch_bounds__(256) prepass_kernel(const PairJob* __restrict_
                 return s_acceptor[25 * bb[o - 2] + 5 * bb[o - 1] + bb[o]];
             };
             const bool valid = (i >= 0 && i <= n);
-            const int z = floor ? (valid ? 0 : neg) : (i == 0 ? 0 : neg);
+            const bool start = floor ? valid : i == 0;
             // traceback layout: the start candidate's nibble, and the donor
             // term negated and offset by C's nibble (the kernel adds B's and
             // A's nibble differences when it reads the row again one and two
             // rows later)
-            if (!J.tb)
-                ((int4*)rowp)[rr] = make_int4(tr, z, P.r + dpen(i + 1), apen(i));
-            else
-                ((int4*)rowp)[rr] = make_int4(tr, z + 15, 5 - 16 * (P.r + dpen(i + 1)),
-                                              16 * apen(i));
+            const int z = (start ? zero : neg) + (J.tb ? 15 : 0);
+            const int rd = J.tb ? 5 - 16 * (P.r + dpen(i + 1)) : P.r + dpen(i + 1);
+            const int ac = J.tb ? 16 * apen(i) : apen(i);
+            tr = prof_offset(J.K, J.tb != 0, tr);  // where the DP kernel reads its scores
+            ((int4*)rowp)[rr] = J.f32 ? make_int4(tr, z, __float_as_int((float)rd),
+                                                  __float_as_int((float)ac))
+                                      : make_int4(tr, z, rd, ac);
         }
         atomicMax(&s_len, (int)at + kPrepassRows * 16);
     }
@@ -448,21 +452,22 @@ __global__ void rescore_finish_kernel(int n, const mpg_dev_result* __restrict__ 
 
 }  // namespace dev
 
-hipError_t launch_dp_k1(hipStream_t, int, bool, const DevParams&, const PairJob*, const int2*, int,
-                        int*, void*, int*, const uint8_t*, const uint8_t*, int2*, uint8_t*,
-                        const DpSink&);
-hipError_t launch_dp_k2(hipStream_t, int, bool, const DevParams&, const PairJob*, const int2*, int,
-                        int*, void*, int*, const uint8_t*, const uint8_t*, int2*, uint8_t*,
-                        const DpSink&);
-hipError_t launch_dp_k4(hipStream_t, int, bool, const DevParams&, const PairJob*, const int2*, int,
-                        int*, void*, int*, const uint8_t*, const uint8_t*, int2*, uint8_t*,
-                        const DpSink&);
-hipError_t launch_dp_p1(hipStream_t, int, bool, const DevParams&, const PairJob*, const int2*, int,
-                        int*, void*, int*, const uint8_t*, const uint8_t*, int2*, uint8_t*,
-                        const DpSink&);
-hipError_t launch_dp_p2(hipStream_t, int, bool, const DevParams&, const PairJob*, const int2*, int,
-                        int*, void*, int*, const uint8_t*, const uint8_t*, int2*, uint8_t*,
-                        const DpSink&);
+// One translation unit per strip width, query kind and value form.
+#define MPG_DP_UNIT(NAME)                                                                       \
+    hipError_t NAME(hipStream_t, int, bool, const DevParams&, const PairJob*, const int2*, int, \
+                    int*, void*, int*, const uint8_t*, const uint8_t*, int2*, uint8_t*,         \
+                    const DpSink&);
+MPG_DP_UNIT(launch_dp_k1)
+MPG_DP_UNIT(launch_dp_k2)
+MPG_DP_UNIT(launch_dp_k4)
+MPG_DP_UNIT(launch_dp_p1)
+MPG_DP_UNIT(launch_dp_p2)
+MPG_DP_UNIT(launch_dp_k1_int)
+MPG_DP_UNIT(launch_dp_k2_int)
+MPG_DP_UNIT(launch_dp_k4_int)
+MPG_DP_UNIT(launch_dp_p1_int)
+MPG_DP_UNIT(launch_dp_p2_int)
+#undef MPG_DP_UNIT
 
 int dp_lds_bytes(int K, bool tb) {
     if (K == 1) return tb ? LdsLayout<1, true>::WAVE : LdsLayout<1, false>::WAVE;
@@ -480,24 +485,20 @@ hipError_t launch_prepass(hipStream_t s, const PairJob* jobs, const int64_t* row
     return hipGetLastError();
 }
 
-hipError_t launch_dp(hipStream_t s, int K, bool tb, bool pro, int ncu, const DevParams& P,
-                     const PairJob* jobs, const int2* items, int nitems, int* qhead, void* pst,
-                     int* prog, const uint8_t* prot, const uint8_t* desc, int2* bnd,
-                     uint8_t* tbbuf, const DpSink& sink) {
+hipError_t launch_dp(hipStream_t s, int K, bool tb, bool pro, bool f32, int ncu,
+                     const DevParams& P, const PairJob* jobs, const int2* items, int nitems,
+                     int* qhead, void* pst, int* prog, const uint8_t* prot, const uint8_t* desc,
+                     int2* bnd, uint8_t* tbbuf, const DpSink& sink) {
     if (nitems <= 0) return hipSuccess;
-    if (pro) {
-        switch (K) {
-            case 1: return launch_dp_p1(s, ncu, tb, P, jobs, items, nitems, qhead, pst, prog, prot, desc, bnd, tbbuf, sink);
-            case 2: return launch_dp_p2(s, ncu, tb, P, jobs, items, nitems, qhead, pst, prog, prot, desc, bnd, tbbuf, sink);
-            default: return hipErrorInvalidValue;
-        }
-    }
-    switch (K) {
-        case 1: return launch_dp_k1(s, ncu, tb, P, jobs, items, nitems, qhead, pst, prog, prot, desc, bnd, tbbuf, sink);
-        case 2: return launch_dp_k2(s, ncu, tb, P, jobs, items, nitems, qhead, pst, prog, prot, desc, bnd, tbbuf, sink);
-        case 4: return launch_dp_k4(s, ncu, tb, P, jobs, items, nitems, qhead, pst, prog, prot, desc, bnd, tbbuf, sink);
-        default: return hipErrorInvalidValue;
-    }
+    auto unit = K == 1   ? (pro ? (f32 ? launch_dp_p1 : launch_dp_p1_int)
+                                : (f32 ? launch_dp_k1 : launch_dp_k1_int))
+                : K == 2 ? (pro ? (f32 ? launch_dp_p2 : launch_dp_p2_int)
+                                : (f32 ? launch_dp_k2 : launch_dp_k2_int))
+                : K == 4 && !pro ? (f32 ? launch_dp_k4 : launch_dp_k4_int)
+                                 : nullptr;
+    if (!unit) return hipErrorInvalidValue;
+    return unit(s, ncu, tb, P, jobs, items, nitems, qhead, pst, prog, prot, desc, bnd, tbbuf,
+                sink);
 }
 
 hipError_t launch_init(hipStream_t s, const PairJob* jobs, int npairs, void* pst, int* prog,

@@ -218,6 +218,7 @@ struct Group {
     int K;
     bool tb;
     bool i16;
+    bool f32;  // the pairs' values as fp32 numbers
     int mode;  // kernel variant of the group's pairs (EXTEND_LEFT pairs run in GLOBAL's)
     size_t off, cnt;  // its work items in Plan::items
 };
@@ -325,9 +326,10 @@ int env_int(const char* name) {
 struct Overrides {
     int K = 0, K16 = 0;
     bool no_seg = false;  // MPG_NO_SEG_PACK=1: every last strip in a wavefront of its own
+    bool no_f32 = false;  // MPG_NO_F32=1: every pair's values as integers
     Overrides()
         : K(env_int("MPG_FORCE_K")), K16(env_int("MPG_FORCE_K16")),
-          no_seg(env_int("MPG_NO_SEG_PACK") != 0) {}
+          no_seg(env_int("MPG_NO_SEG_PACK") != 0), no_f32(env_int("MPG_NO_F32") != 0) {}
 };
 
 // Planning choices made by mpg_autotune from timed runs (0: not tuned).
@@ -394,6 +396,9 @@ int64_t tb_bytes_max(int n, int m) {
 struct BoundInfo {
     int64_t maxpos = 0, pmax = 0;
     int64_t pfix = 0;  // the penalties a profile does not replace: f, r + d + a
+    int64_t gopen = 0, gext = 0;  // open + first extension, and extension, of a gap
+    int64_t fs = 0, intron = 0;   // f; r + the largest d + the largest a
+    bool introns = true;
     explicit BoundInfo(const mpg_params* p) {
         int mp = 0, mn = 0;
         for (int a = 0; a < 24; ++a)
@@ -406,6 +411,11 @@ struct BoundInfo {
             dmax = std::max<int>(dmax, p->donor[k]);
             amax = std::max<int>(amax, p->acceptor[k]);
         }
+        gopen = (int64_t)p->q + p->e;
+        gext = p->e;
+        fs = p->f;
+        intron = (int64_t)p->r + dmax + amax;
+        introns = !(p->flags & MPG_NO_INTRON);
         maxpos = mp;
         pfix = std::max<int64_t>((int64_t)p->f, (int64_t)p->r + dmax + amax);
         pmax = std::max<int64_t>({(int64_t)p->q + p->e, pfix, (int64_t)-mn});
@@ -416,7 +426,27 @@ struct BoundInfo {
         BoundInfo b = *this;
         b.maxpos = std::max<int64_t>(0, smax);
         b.pmax = std::max(pfix, gmax);
+        b.gopen = b.gext = gmax;
         return b;
+    }
+    // The fp32 form of the DP kernels' values (see Sentinel in mpg_dp.h): every
+    // reachable H and state is an exact integer in its range.  LOCAL: H lies
+    // in [0, maxpos * m], and a state below 0 is never on a path, so the upper
+    // end must stay below 2^24 (2^23 above the number for 0) and the sentinel
+    // less two penalties above 0.  The other modes: above, as LOCAL with half
+    // the range; below, every reachable cell (i, j) is reached at the cost of
+    // one intron to row i (or one frameshift and a gap of i/3 codons) and one
+    // gap of j residues, and a state lies at most one intron or gap opening
+    // below its cell; the sentinel, which drifts by at most its diagonal's
+    // scores, must stay below the line and above 0.
+    bool f32_ok(int64_t n, int64_t m, int mode, bool tb) const {
+        const int64_t sc = tb ? 16 : 1;
+        const int64_t up = sc * (maxpos * (m + 1) + 2);
+        if (mode == MPG_LOCAL) return up < (1 << 23) && sc * pmax * 4 < (1 << 22);
+        const int64_t cell = introns ? intron + gopen + gext * (m + 1)
+                                     : fs + 2 * gopen + gext * ((n + 2) / 3 + m + 1);
+        const int64_t low = cell + std::max(intron, gopen + gext) + fs + 2 * 128;
+        return up < (1 << 22) && sc * low < (1 << 22) && sc * pmax * 4 < (1 << 21);
     }
     bool ok(int64_t n, int64_t m, int mode) const {
         const int64_t lim = (int64_t)1 << 24;
@@ -449,6 +479,17 @@ void make_dev_params(const mpg_params* p, DevParams* d) {
     std::memcpy(d->gcode, p->gcode, 64);
     std::memcpy(d->donor, p->donor, 125);
     std::memcpy(d->acceptor, p->acceptor, 125);
+    for (int tb = 0; tb < 2; ++tb) {
+        const int64_t q = p->q, e = p->e, f = p->f;
+        const int32_t v[6] = {(int32_t)(tb ? 16 * (q + e) - 13 : q), (int32_t)(tb ? 16 * (q + e) - 12 : q),
+                              (int32_t)(tb ? 16 * e : e), (int32_t)(tb ? 16 * f : f),
+                              (int32_t)(16 * f - 11), (int32_t)(16 * f - 9)};
+        for (int k = 0; k < 6; ++k) {
+            const float x = (float)v[k];
+            d->pen[0][tb][k] = v[k];
+            std::memcpy(&d->pen[1][tb][k], &x, 4);
+        }
+    }
     d->max_polls = kMaxPolls;
     // debug override for tests of the failure path: MPG_DEBUG_WAIT_POLLS=0
     // makes every bounded wait between strips give up at once (its pairs
@@ -542,7 +583,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     const KChoice kc = choose_widths(ov, cfg.tune, cfg.force_K);
     std::vector<std::pair<int64_t, int32_t>>& e16 = P.e16;
     e16.clear();
-    // One group per (width, traceback, kernel mode), in order of first
+    // One group per (width, traceback, kernel mode, value form), in order of first
     // appearance in the queue order, its items counted first and then written
     // in place.  The two fixed-end modes share a kernel (EXTEND_LEFT's start term is read
     // per pair); with per-pair modes every mode but LOCAL runs in the mixed
@@ -554,7 +595,8 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     };
     auto gkey = [&](const PairJob& J) {
         const int gm = gmode(J.mode) == kModeMixed ? 3 : gmode(J.mode);  // 0, 1, 2 or 3
-        return ((J.K == 1 ? 0 : J.K == 2 ? 1 : 2) * 2 + (J.tb ? 1 : 0)) * 4 + gm;
+        return (((J.K == 1 ? 0 : J.K == 2 ? 1 : 2) * 2 + (J.tb ? 1 : 0)) * 4 + gm) * 2 +
+               (J.f32 ? 1 : 0);
     };
     // per job: group key << 24 | traceback << 23 | strips (a compact copy for
     // the passes in queue order, which visit the jobs out of order)
@@ -581,7 +623,6 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.prot_off = s.prot_off;
         J.status = MPG_OK;
         J.mode = cfg.modes ? cfg.modes[idx[k]] : p->mode;
-        J._pad = 0;
         const BoundInfo bk = cfg.pro ? bound.profile(cfg.pro_bounds[2 * idx[k]],
                                                      cfg.pro_bounds[2 * idx[k] + 1])
                                      : bound;
@@ -598,6 +639,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         const int nsteps = pair_nsteps(nn, mm, K);
         J.nchunks = nsteps / 64;
         J.nstrips = (mm + 1 + 64 * K - 1) / (64 * K);
+        J.f32 = !ov.no_f32 && bk.f32_ok(nn, mm, J.mode, J.tb != 0) ? 1 : 0;
         if (J.tb && J.status == MPG_OK && (uint64_t)tb_bytes_of(nn, mm, K) > tb_budget)
             J.status = MPG_E_RANGE;
         J.ops_off = ops_off[idx[k]];
@@ -624,7 +666,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.prog_off = (int32_t)P.nprog;
         P.nprog += J.nstrips;
         P.ginfo[k] = (uint32_t)gkey(J) << 24 | (uint32_t)(J.tb ? 1 : 0) << 23 | (uint32_t)J.nstrips;
-        // lane-segment class (traceback, width, chunks), then lanes
+        // lane-segment class (value form, traceback, width, chunks), then lanes
         // descending; a pair has fewer than 2^15 chunks (genome rows are
         // below 2^21).  Traced pairs only in batch calls (serving walks each
         // pair in the wavefront that finishes it).
@@ -633,7 +675,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
             gmode(J.mode) == MPG_LOCAL) {
             const int u = last_lanes(J);
             if (u >= 1 && u <= 63)
-                P.seg_key[k] = (J.tb << 23) | ((K == 1 ? 0 : K == 2 ? 1 : 2) << 21) |
+                P.seg_key[k] = (J.f32 << 24) | (J.tb << 23) | ((K == 1 ? 0 : K == 2 ? 1 : 2) << 21) |
                                (J.nchunks << 6) | (63 - u);
         }
         bysize.push_back({(int64_t)J.nstrips * J.nchunks, k});
@@ -641,9 +683,9 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     // batches: longest pair first (the last pairs to finish are the short
     // ones); serving: shortest first (short results are out early)
     sort_by_key(bysize, !shortest_first, P.sort_tmp, P.sort_cnt);
-    int gidx[24];
-    int64_t gcount[24] = {0};
-    std::fill(gidx, gidx + 24, -1);
+    int gidx[48];
+    int64_t gcount[48] = {0};
+    std::fill(gidx, gidx + 48, -1);
     int64_t nwalk = 0;
     for (auto& e : bysize) {
         const uint32_t gi = P.ginfo[e.second];
@@ -651,7 +693,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         if (gidx[key] < 0) {
             const PairJob& J = P.jobs[e.second];
             gidx[key] = (int)P.groups.size();
-            P.groups.push_back(Group{J.K, J.tb != 0, false, gmode(J.mode), 0, 0});
+            P.groups.push_back(Group{J.K, J.tb != 0, false, J.f32 != 0, gmode(J.mode), 0, 0});
         }
         gcount[gidx[key]] += gi & 0x7FFFFF;
         nwalk += (gi >> 23) & 1;
@@ -725,7 +767,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     // int16 pairs: neighbours in size order share a pack
     if (!e16.empty()) {
         sort_by_key(e16, true, P.sort_tmp, P.sort_cnt);
-        P.groups.push_back(Group{K16, false, true, MPG_LOCAL, P.items.size(), 0});
+        P.groups.push_back(Group{K16, false, true, false, MPG_LOCAL, P.items.size(), 0});
         for (size_t q = 0; q < e16.size(); q += 2) {
             const PairJob& A = P.jobs[e16[q].second];
             const bool hasB = q + 1 < e16.size();
@@ -1090,7 +1132,7 @@ int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg,
             return launch_dp16(s2, G.K, cfg.ncu, DG, X.d_jobs, X.d_packs, X.d_items + X.goff[g],
                                nit, X.d_qhead + g, X.d_pst, X.d_prog, X.d_prot,
                                X.d_desc, X.d_bnd, sink);
-        return launch_dp(s2, G.K, G.tb, cfg.pro, cfg.ncu, DG, X.d_jobs, X.d_items + X.goff[g],
+        return launch_dp(s2, G.K, G.tb, cfg.pro, G.f32, cfg.ncu, DG, X.d_jobs, X.d_items + X.goff[g],
                          nit,
                          X.d_qhead + g, X.d_pst, X.d_prog, X.d_prot, X.d_desc, X.d_bnd,
                          X.d_tb, sink);
