@@ -343,19 +343,12 @@ struct Tuning {
 // Columns per lane: one width for the pairs of a call wider than 64 columns
 // (pairs of one width share a launch; mixed widths would split the device
 // between concurrent persistent launches): a forced width, else the tuned
-// one, else 2.  Pairs of at most 64 columns take width 1.
-struct KChoice {
-    int K[2] = {2, 2};  // [traceback]
-};
-
-KChoice choose_widths(const Overrides& ov, const Tuning* tu, int force) {
-    KChoice kc;
-    int K = 2;
-    if (ov.K == 1 || ov.K == 2 || ov.K == 4) K = ov.K;
-    else if (force) K = force;
-    else if (tu && tu->K) K = tu->K;
-    kc.K[0] = kc.K[1] = K;
-    return kc;
+// one, else 0: the call's own work decides (width_by_work).  Pairs of at most
+// 64 columns take width 1.
+int choose_width(const Overrides& ov, const Tuning* tu, int force) {
+    if (ov.K == 1 || ov.K == 2 || ov.K == 4) return ov.K;
+    if (force) return force;
+    return tu ? tu->K : 0;
 }
 
 // Columns per lane of the int16 kernel (one width for a whole call: pairs of
@@ -388,6 +381,36 @@ int64_t tb_bytes_of(int n, int m, int K) {
 int64_t tb_bytes_max(int n, int m) {
     return std::max({tb_bytes_of(n, m, 1), tb_bytes_of(n, m, 2), tb_bytes_of(n, m, 4)});
 }
+
+// Width 1 or 2 for a call, from what bounds it.  A call takes at least its
+// work (strips x steps) spread over the device's SIMDs, and at least the
+// longest pair's own chain: its steps one after another, each strip 128 steps
+// behind the one on its left.  Width 2 does a column's work in fewer
+// instructions, width 1 makes a step shorter.  Cycles of one step, measured on
+// the 10k batch's pairs: on a SIMD shared by four wavefronts 149 and 93
+// (score-only), 250 and 133 (traceback); alone, 245 and 165, 390 and 250.
+// Times at widths 2 and 1: one traced pair 0.56 and 0.39 ms, 800 traced pairs
+// 4.74 and 3.41, 3,000 6.35 and 6.45, 6,000 11.2 and 11.9; score-only 1,500
+// pairs 3.5 and 2.45, 3,000 3.67 and 4.04, 10,000 10.2 and 12.5 ms.
+struct WidthWork {
+    double work[2] = {0, 0}, chain[2] = {0, 0};  // [0]: width 1, [1]: width 2
+    void add(int n, int m, bool tb) {
+        static constexpr double kShared[2][2] = {{93, 149}, {133, 250}};
+        static constexpr double kAlone[2][2] = {{165, 245}, {250, 390}};
+        for (int w = 0; w < 2; ++w) {
+            const int K = w + 1;
+            const double steps = pair_nsteps(n, m, K);
+            const double strips = (m + 64 * K) / (64 * K);
+            work[w] += kShared[tb][w] * steps * strips;
+            chain[w] = std::max(chain[w], kAlone[tb][w] * (steps + 128 * (strips - 1)));
+        }
+    }
+    int width(int ncu) const {
+        const double t1 = std::max(work[0] / (4 * ncu), chain[0]);
+        const double t2 = std::max(work[1] / (4 * ncu), chain[1]);
+        return t1 < t2 ? 1 : 2;
+    }
+};
 
 // Bound on |value| of reachable cells (see the public header): the largest
 // match score times the protein length, and (EXTEND/GLOBAL, whose H has no 0
@@ -509,6 +532,7 @@ struct RunCfg {
                         // the traceback and publishes the record (status
                         // last) to memory the host polls; shortest pairs first
     const Tuning* tune = nullptr;  // measured costs for choosing K
+    bool wide = false;               // not tuned: width 2, whatever the work
     int force_K = 0, force_K16 = 0;  // calibration runs: one width for all
     const int8_t* modes = nullptr;   // per pair of the call: its boundary mode
                                      // (NULL: params.mode for every pair)
@@ -580,7 +604,19 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     const BoundInfo bound(p);
     const bool allow16 = (p->flags & MPG_ALLOW_I16) != 0 && !cfg.pro;
     const int K16 = choose_K16(ov, cfg.tune, cfg.force_K16);
-    const KChoice kc = choose_widths(ov, cfg.tune, cfg.force_K);
+    int width = choose_width(ov, cfg.tune, cfg.force_K);
+    const bool by_work = width == 0 && !cfg.wide;
+    if (by_work) {
+        WidthWork ww;
+        for (int32_t k = 0; k < cnt; ++k) {
+            const mpg_seg& s = segs[idx[k]];
+            ww.add(std::max(0, s.dlen), std::max(0, s.plen),
+                   ((s.flags | p->flags) & MPG_WANT_TB) != 0);
+        }
+        width = ww.width(cfg.ncu);
+    } else if (width == 0) {
+        width = 2;
+    }
     std::vector<std::pair<int64_t, int32_t>>& e16 = P.e16;
     e16.clear();
     // One group per (width, traceback, kernel mode, value form), in order of first
@@ -633,7 +669,11 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         const int nn = std::max(0, J.n), mm = std::max(0, J.m);
         // a pair whose columns fit one strip of 64 takes one column per lane:
         // wider lanes would only add idle columns to every step
-        int K = (mm + 1 <= narrow && !ov.K && !cfg.force_K) ? 1 : kc.K[want_tb ? 1 : 0];
+        int K = (mm + 1 <= narrow && !ov.K && !cfg.force_K) ? 1 : width;
+        // (at the traceback budget's edge, the width that needs less)
+        if (by_work && K == 1 && mm + 1 > narrow && want_tb &&
+            (uint64_t)tb_bytes_of(nn, mm, 1) > tb_budget)
+            K = 2;
         if (cfg.pro && K > 2) K = 2;  // profile kernels come in widths 1 and 2
         J.K = K;
         const int nsteps = pair_nsteps(nn, mm, K);
@@ -1455,6 +1495,12 @@ int mpg_align_batch_dev_noalloc(mpg_ctx* ctx, const mpg_params* p, const uint8_t
     const FixedScratch fx{ctx->scratch, kScratchBytes, &na.stage};
     rc = prepare(ctx->stream, ctx->ws, p, d_prot, d_dna, segs, na.idx.data(), n, na.ops_off,
                  d_out, d_ops, cfg, X, &fx);
+    if (rc == MPG_E_RANGE && !cfg.wide) {
+        // width 1 may need slightly more scratch than width 2
+        cfg.wide = true;
+        rc = prepare(ctx->stream, ctx->ws, p, d_prot, d_dna, segs, na.idx.data(), n, na.ops_off,
+                     d_out, d_ops, cfg, X, &fx);
+    }
     // every kernel variant on the context's stream, one after another
     if (rc == MPG_OK) rc = enqueue(ctx->stream, ctx->ws, X, cfg, false);
     std::swap(X.P, na.plan);
