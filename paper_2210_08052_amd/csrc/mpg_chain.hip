@@ -6,16 +6,27 @@
 // their ranking.
 //
 // One workgroup per anchor set: one wavefront, or four when the launch's
-// largest set has 512 anchors or more (its candidate loops are the launch's
-// critical path).  f of the set's anchors lives in LDS (fp64), or, for a set
-// too large for it, in the f output in HBM, read and written with
-// device-scope atomics so that no wavefront reads a stale copy from its
-// vector cache.  For anchor j the workgroup's threads take the candidates
-// i < j in a strided loop, keep their best (value, first index), and a wave
-// reduction, then (several wavefronts) a reduction over the wavefronts' bests
-// in LDS, picks the maximum (ties: smaller i).  Extraction repeats an arg-max
-// over the unused anchors and lets thread 0 follow the predecessors; ranking
-// repeats an arg-max over the extracted chains.
+// largest set has 512 anchors or more (its chain of anchors is the launch's
+// critical path).  Anchors go 64 at a time, one per lane.  First every lane
+// takes the candidates before the block (the wavefronts share them, nearest
+// first): all lanes look at the same candidate at once, so nothing is reduced
+// across lanes, and a candidate costs one comparison unless some lane may
+// still gain by it: its value is at most f(i) + k, since the gap penalty is
+// never negative, and only a candidate that may reach a lane's best pays for
+// the gap and its log2.  The scan ends where the genome distance alone
+// exceeds G.  Then the block's own anchors are settled one after another, each
+// offered to the lanes behind it.  (One anchor at a time, the lanes striding
+// over its candidates and an arg-max over the workgroup, took 3.4 us per
+// anchor of the largest set: 2.42 ms for 3,000 sets of up to 700 anchors.)
+//
+// f of the set's anchors lives in LDS (fp64), or, for a set too large for it,
+// in the f output in HBM, read and written with device-scope atomics so that
+// no wavefront reads a stale copy from its vector cache.  Extraction takes the
+// unused anchor of largest f again and again and follows its predecessors; the
+// ranking takes the best chain again and again.  A set held in LDS does both
+// in one wavefront, each lane keeping the best of every 64th anchor or chain,
+// so that a round is one arg-max and a rescan of the lanes that lost an
+// anchor; a larger set scans all its anchors in every round.
 #include "mpg_internal.h"
 
 namespace mpg {
@@ -40,6 +51,16 @@ __device__ __forceinline__ double chain_gamma(long long g, double beta) {
     const double lg = beta * log2(a + 1.0);
     if (g > 0) return third + lg;
     return third < lg ? third : lg;
+}
+
+// A number not above chain_gamma(g, beta): its terms in fp32, less more than
+// their rounding (every term is at least 1/3 or beta, the relative errors of
+// the conversions, products and log2 are below 1e-6 in all).
+__device__ __forceinline__ double gamma_low(long long g, float beta) {
+    if (g == 0) return 0.0;
+    const float a = (float)(g < 0 ? -g : g);
+    const float third = a * 0.333333f, lg = beta * __log2f(a + 1.0f);
+    return (double)((g > 0 ? third + lg : fminf(third, lg)) * 0.99999f);
 }
 
 // Wave-wide arg-max of (v, i): the larger v, ties the smaller i (i < 0: none).
@@ -78,6 +99,39 @@ __device__ __forceinline__ void block_argmax(double& v, int& i, double* rv, int*
         }
         __syncthreads();  // the slots are free again
     }
+}
+
+// Wave-wide maximum of an unsigned value (row shifts, then row broadcasts;
+// lanes without a source keep 0, the identity).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define MPG_DPP_MAX(CTRL)                                                                   \
+    {                                                                                       \
+        const uint32_t o =                                                                  \
+            (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);        \
+        v = o > v ? o : v;                                                                  \
+    }
+    MPG_DPP_MAX(0x111)  // row_shr:1
+    MPG_DPP_MAX(0x112)
+    MPG_DPP_MAX(0x114)
+    MPG_DPP_MAX(0x118)
+    MPG_DPP_MAX(0x142)  // row_bcast:15
+    MPG_DPP_MAX(0x143)  // row_bcast:31
+#undef MPG_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Arg-max over the wavefront of (v, i), i < 0: none: the larger v, ties the
+// smaller i.  A double's bits, the sign bit set (positive) or all inverted
+// (negative), order the numbers as unsigned integers.
+__device__ __forceinline__ int wave_best(double v, int i) {
+    const long long b = __double_as_longlong(v);
+    const unsigned long long u =
+        i < 0 ? 0ull : (unsigned long long)b ^ (b < 0 ? ~0ull : 1ull << 63);
+    const uint32_t hi = (uint32_t)(u >> 32), lo = (uint32_t)u;
+    const uint32_t mh = wave_max_u32(hi);
+    const uint32_t ml = wave_max_u32(hi == mh ? lo : 0u);
+    // the smallest index is the largest complement; none: 0
+    return (int)~wave_max_u32(i >= 0 && hi == mh && lo == ml ? ~(uint32_t)i : 0u);
 }
 
 __device__ __forceinline__ double ld_f64_dev(const double* p) {
@@ -138,37 +192,218 @@ __global__ void __launch_bounds__(64 * W) chain_kernel(const ChainSetJob* __rest
     }
     const int2* AA = stage ? (const int2*)sA : A;
     const double kd = (double)cfg.k;
-    // ---- the DP, anchor by anchor
-    for (int j = 0; j < n; ++j) {
-        const int2 aj = AA[j];
-        double bv = 0.0;
+    // ---- the DP, 64 anchors at a time
+    const int lane = tid & 63, wave = tid >> 6;
+    double* mv = (double*)(smem + kChainRedBytes - 64 * 12 * 3);  // the other wavefronts' bests
+    int* mi = (int*)(mv + 64 * 3);
+    // beyond this genome distance (in x units) |g| >= G whatever the residues
+    long long ylo = 0, yhi = 0;
+    for (int i = lane; i < n; i += 64) {
+        const long long y = AA[i].y;
+        if (i == lane) ylo = yhi = y;
+        ylo = y < ylo ? y : ylo;
+        yhi = y > yhi ? y : yhi;
+    }
+    if (lane >= n) ylo = yhi = n ? AA[0].y : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const long long a = __shfl_xor(ylo, o), b = __shfl_xor(yhi, o);
+        ylo = a < ylo ? a : ylo;
+        yhi = b > yhi ? b : yhi;
+    }
+    const long long reach = (long long)cfg.G + 3 * (yhi - ylo);
+    auto too_far = [&](long long dx) { return (cfg.binned ? 256 * (dx - 1) : dx) >= reach; };
+    // (a beta beyond fp32 bounds nothing: 0 is a bound too)
+    const float beta_f = cfg.beta < 1e30 ? (float)cfg.beta : 0.0f;
+    for (int j0 = 0; j0 < n; j0 += 64) {
+        const int j = j0 + lane;
+        const bool live = j < n;
+        const int2 aj = AA[live ? j : n - 1];
+        double bv = kd;
         int bi = -1;
-        for (int i = tid; i < j; i += NT) {
-            const int2 ai = AA[i];
+        // candidate i = (ai, fi) offered to the lanes in `open`; `last`: of
+        // equal values the one offered later wins (smaller i: descending scan)
+        auto offer = [&](const int2 ai, double fi, int i, bool open, bool last) {
+            const bool may = open && (last ? fi + kd >= bv : fi + kd > bv);
+            if (!__any(may)) return;
+            bool ok = may && aj.x >= ai.x && aj.y > ai.y;
+            if (!__any(ok)) return;
             const long long dx = (long long)aj.x - ai.x, dy = (long long)aj.y - ai.y;
-            if (dx < 0 || dy <= 0) continue;
             const long long g = chain_gap(dx, dy, cfg.binned);
-            if (g >= cfg.G || -g >= cfg.G) continue;
-            const double v = (fget(i) + (double)(dy < cfg.k ? dy : cfg.k)) - chain_gamma(g, cfg.beta);
-            if (bi < 0 || v > bv) {
+            const double u = fi + (double)(int)(dy < cfg.k ? dy : cfg.k);
+            ok = ok && g < cfg.G && -g < cfg.G;
+            // the exact penalty (a division and a log2 in fp64) only where a
+            // lower bound of it leaves the candidate in
+            const double most = u - gamma_low(g, beta_f);
+            ok = ok && (last ? most >= bv : most > bv);
+            if (!__any(ok)) return;
+            double v = u;
+            if (__any(ok && g != 0)) v = u - chain_gamma(ok ? g : 0, cfg.beta);
+            if (ok && (v > bv || (last && v == bv && bi >= 0))) {
                 bv = v;
                 bi = i;
             }
-        }
-        block_argmax<W>(bv, bi, rv, ri);
-        if (tid == 0) {
-            const bool link = bi >= 0 && bv > kd;
-            const double fj = link ? bv : kd;
-            if (f_lds) {
-                f[j] = fj;
-                fo[j] = fj;
-            } else {
-                st_f64_dev(fo + j, fj);
+        };
+        // the anchors before the block, in chunks of 64, nearest first
+        const int x0 = AA[j0].x;
+        for (int c = j0 / 64 - 1 - wave; c >= 0; c -= W) {
+            if (too_far((long long)x0 - AA[c * 64 + 63].x)) break;
+            for (int q = 56; q >= 0; q -= 8) {
+                int2 ai[8];
+                double fi[8];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    ai[r] = AA[c * 64 + q + r];
+                    fi[r] = fget(c * 64 + q + r);
+                }
+#pragma unroll
+                for (int r = 7; r >= 0; --r) offer(ai[r], fi[r], c * 64 + q + r, live, true);
             }
-            po[j] = link ? bi : -1;
-            if (stage) spo[j] = link ? bi : -1;
+        }
+        if constexpr (W > 1) {
+            if (wave > 0) {
+                mv[(wave - 1) * 64 + lane] = bv;
+                mi[(wave - 1) * 64 + lane] = bi;
+            }
+            __syncthreads();
+        }
+        if (wave == 0) {
+#pragma unroll
+            for (int w = 0; w + 1 < W; ++w) {
+                const double v2 = mv[w * 64 + lane];
+                const int i2 = mi[w * 64 + lane];
+                if (i2 >= 0 && (v2 > bv || (v2 == bv && i2 < bi))) {
+                    bv = v2;
+                    bi = i2;
+                }
+            }
+            // the block's own anchors, each once it is settled
+            const int cnt = n - j0 < 64 ? n - j0 : 64;
+            for (int t = 0; t + 1 < cnt; ++t) {
+                const long long fb = __double_as_longlong(bv);
+                const int flo = __builtin_amdgcn_readlane((int)fb, t);
+                const int fhi = __builtin_amdgcn_readlane((int)(fb >> 32), t);
+                const double fi = __longlong_as_double(((long long)fhi << 32) | (uint32_t)flo);
+                const int2 ai = make_int2(__builtin_amdgcn_readlane(aj.x, t),
+                                          __builtin_amdgcn_readlane(aj.y, t));
+                offer(ai, fi, j0 + t, live && lane > t, false);
+            }
+            if (live) {
+                if (f_lds) {
+                    f[j] = bv;
+                    fo[j] = bv;
+                } else {
+                    st_f64_dev(fo + j, bv);
+                }
+                po[j] = bi;
+                if (stage) spo[j] = bi;
+            }
         }
         __syncthreads();
+    }
+    if (stage) {
+        // ---- extraction and ranking in one wavefront; a used anchor's f is
+        // negated in LDS, and the chains' scores take the anchors' place
+        if (wave > 0) return;
+        double* sc = (double*)sA;
+        ChainRec* R = recs + S.off;  // at most n chains
+        int* idx = idx_out + S.off;
+        double lv = 0.0;
+        int li = -1;  // the best unused anchor among lane, lane + 64, ...
+        auto rescan = [&]() {
+            lv = 0.0;
+            li = -1;
+            int i = lane;
+            for (; i + 7 * 64 < n; i += 8 * 64) {  // eight reads in flight
+                double fi[8];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) fi[r] = f[i + 64 * r];
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    if (fi[r] > lv) {
+                        lv = fi[r];
+                        li = i + 64 * r;
+                    }
+            }
+            for (; i < n; i += 64) {
+                const double fi = f[i];
+                if (fi > lv) {
+                    lv = fi;
+                    li = i;
+                }
+            }
+        };
+        rescan();
+        int nc = 0, pos = 0;
+        for (;;) {
+            const int bi = wave_best(lv, li);
+            if (bi < 0) break;
+            // every lane follows the chain; lane 0 marks it
+            const double top_f = f[bi];
+            int len = 0, t = bi;
+            unsigned long long lost = 0;
+            double stop_f = 0.0;
+            while (t >= 0) {
+                const double ft = f[t];
+                if (!(ft > 0.0)) {
+                    stop_f = -ft;
+                    break;
+                }
+                if (lane == 0) f[t] = -ft;
+                lost |= 1ull << (t & 63);
+                ++len;
+                t = spo[t];
+            }
+            // indices ascending: written from the end of the chain's range
+            int u = bi;
+            for (int q = len - 1; q >= 0; --q) {
+                if (lane == 0) idx[pos + q] = u;
+                u = spo[u];
+            }
+            const double score = top_f - stop_f;
+            if (lane == 0) {
+                sc[nc] = score;
+                ChainRec c;
+                c.score = score;
+                c.first = pos;
+                c.len = len;
+                R[nc] = c;
+            }
+            pos += len;
+            ++nc;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if ((lost >> lane) & 1) rescan();
+        }
+        const int keep = nc < cfg.max_chains ? nc : cfg.max_chains;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        auto rescan_chains = [&]() {
+            lv = -INFINITY;
+            li = -1;
+            for (int c = lane; c < nc; c += 64) {
+                const double v = sc[c];
+                if (v > lv) {  // -infinity: taken
+                    lv = v;
+                    li = c;
+                }
+            }
+        };
+        rescan_chains();
+        for (int r = 0; r < keep; ++r) {
+            const int bc = wave_best(lv, li);
+            if (bc < 0) break;
+            if (lane == (bc & 63)) {
+                const ChainRec c = R[bc];
+                mpg_chain_out o;
+                o.score = c.score;
+                o.first = c.first;
+                o.len = c.len;
+                top[(int64_t)s * cfg.max_chains + r] = o;
+                sc[bc] = -INFINITY;
+                rescan_chains();
+            }
+        }
+        if (lane == 0) ntop[s] = keep;
+        return;
     }
     // ---- extraction: the unused anchor of largest f starts a chain that
     // follows the predecessors until -1 or a used anchor

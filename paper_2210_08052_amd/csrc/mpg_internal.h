@@ -219,10 +219,11 @@ struct ChainSetJob {
     int32_t id;      // the set's index in the call (its ntop and top slots)
     int32_t _pad;
 };
-// LDS of the chaining kernel (at most 64 KB): the reduction slots, then per
+// LDS of the chaining kernel (at most 64 KB): the reduction slots and the
+// bests that three wavefronts hand to the first (64 x 12 bytes each), then per
 // anchor the used flag (1 byte), f (8) when it fits, and the anchor (8) and
 // its predecessor (4) when those fit too.
-constexpr int kChainRedBytes = 64;
+constexpr int kChainRedBytes = 64 + 3 * 64 * 12;
 constexpr int kChainLdsBytes = 65536;
 struct ChainCfg {
     int32_t k, G, binned, max_chains;
