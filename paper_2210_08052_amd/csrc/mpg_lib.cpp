@@ -279,18 +279,24 @@ struct Workspace {
     }
     hipStream_t side[kSideStreams] = {};
     hipEvent_t fork_ev = nullptr, join_ev[kSideStreams] = {};
-    bool streams_ready = false;
-    int ensure_streams() {
-        if (streams_ready) return MPG_OK;
-        for (int k = 0; k < kSideStreams; ++k) {
-            if (hipStreamCreateWithFlags(&side[k], hipStreamNonBlocking) != hipSuccess)
-                return MPG_E_DEVICE;
-            if (hipEventCreateWithFlags(&join_ev[k], hipEventDisableTiming) != hipSuccess)
-                return MPG_E_DEVICE;
-        }
-        if (hipEventCreateWithFlags(&fork_ev, hipEventDisableTiming) != hipSuccess)
+    // at least n side streams (n <= kSideStreams), their events and the fork's
+    int ensure_streams(int n) {
+        if (!fork_ev && hipEventCreateWithFlags(&fork_ev, hipEventDisableTiming) != hipSuccess) {
+            fork_ev = nullptr;
             return MPG_E_DEVICE;
-        streams_ready = true;
+        }
+        for (int k = 0; k < n; ++k) {
+            if (!side[k] &&
+                hipStreamCreateWithFlags(&side[k], hipStreamNonBlocking) != hipSuccess) {
+                side[k] = nullptr;
+                return MPG_E_DEVICE;
+            }
+            if (!join_ev[k] &&
+                hipEventCreateWithFlags(&join_ev[k], hipEventDisableTiming) != hipSuccess) {
+                join_ev[k] = nullptr;
+                return MPG_E_DEVICE;
+            }
+        }
         return MPG_OK;
     }
     void release() {
@@ -299,15 +305,17 @@ struct Workspace {
         for (auto* b : d) b->release();
         HostBuf* h[] = {&hplan, &hseq, &hout, &hops, &prec, &pops, &hchain, &hcset};
         for (auto* b : h) b->release();
-        if (streams_ready) {
-            for (int k = 0; k < kSideStreams; ++k) {
-                hipStreamSynchronize(side[k]);
-                hipStreamDestroy(side[k]);
-                hipEventDestroy(join_ev[k]);
+        for (int k = 0; k < kSideStreams; ++k) {
+            if (side[k]) {
+                (void)hipStreamSynchronize(side[k]);
+                (void)hipStreamDestroy(side[k]);
+                side[k] = nullptr;
             }
-            hipEventDestroy(fork_ev);
-            streams_ready = false;
+            if (join_ev[k]) (void)hipEventDestroy(join_ev[k]);
+            join_ev[k] = nullptr;
         }
+        if (fork_ev) (void)hipEventDestroy(fork_ev);
+        fork_ev = nullptr;
     }
 };
 
@@ -388,21 +396,26 @@ int64_t tb_bytes_max(int n, int m) {
 // behind the one on its left.  Width 2 does a column's work in fewer
 // instructions, width 1 makes a step shorter.  Cycles of one step, measured on
 // the 10k batch's pairs: on a SIMD shared by four wavefronts 149 and 93
-// (score-only), 250 and 133 (traceback); alone, 245 and 165, 390 and 250.
+// (score-only), 250 and 133 (traceback); alone, 245 and 165, 390 and 250: a
+// part per step and a part per column, of which the intron states are half.
+// (Without introns a step alone mostly waits for the hand-off between lanes:
+// rescoring 100 pairs takes 0.95 ms at width 1, 0.91 at width 2.)
 // Times at widths 2 and 1: one traced pair 0.56 and 0.39 ms, 800 traced pairs
 // 4.74 and 3.41, 3,000 6.35 and 6.45, 6,000 11.2 and 11.9; score-only 1,500
 // pairs 3.5 and 2.45, 3,000 3.67 and 4.04, 10,000 10.2 and 12.5 ms.
 struct WidthWork {
     double work[2] = {0, 0}, chain[2] = {0, 0};  // [0]: width 1, [1]: width 2
-    void add(int n, int m, bool tb) {
-        static constexpr double kShared[2][2] = {{93, 149}, {133, 250}};
-        static constexpr double kAlone[2][2] = {{165, 245}, {250, 390}};
-        for (int w = 0; w < 2; ++w) {
-            const int K = w + 1;
+    void add(int n, int m, bool tb, bool introns) {
+        struct Cost { double step, column; };
+        static constexpr Cost kShared[2][2] = {{{37, 28}, {37, 56}}, {{16, 58}, {16, 117}}};
+        static constexpr Cost kAlone[2][2] = {{{140, 20}, {85, 80}}, {{150, 60}, {110, 140}}};
+        const Cost sh = kShared[tb][introns], al = kAlone[tb][introns];
+        for (int K = 1; K <= 2; ++K) {
             const double steps = pair_nsteps(n, m, K);
             const double strips = (m + 64 * K) / (64 * K);
-            work[w] += kShared[tb][w] * steps * strips;
-            chain[w] = std::max(chain[w], kAlone[tb][w] * (steps + 128 * (strips - 1)));
+            work[K - 1] += (sh.step + sh.column * K) * steps * strips;
+            chain[K - 1] = std::max(chain[K - 1],
+                                    (al.step + al.column * K) * (steps + 128 * (strips - 1)));
         }
     }
     int width(int ncu) const {
@@ -611,7 +624,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         for (int32_t k = 0; k < cnt; ++k) {
             const mpg_seg& s = segs[idx[k]];
             ww.add(std::max(0, s.dlen), std::max(0, s.plen),
-                   ((s.flags | p->flags) & MPG_WANT_TB) != 0);
+                   ((s.flags | p->flags) & MPG_WANT_TB) != 0, bound.introns);
         }
         width = ww.width(cfg.ncu);
     } else if (width == 0) {
@@ -1140,7 +1153,8 @@ int prepare(hipStream_t st, Workspace& ws, const mpg_params* p, const uint8_t* d
 // Device part of a call: only kernel launches (and, with `fork`, event
 // record/wait to run the kernel variants concurrently on side streams), no
 // host synchronisation, allocation or memset, so it may be captured into a
-// graph (with fork = false).
+// graph (with fork, once the workspace has its side streams: the variants
+// become parallel branches of the graph).
 int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg, bool fork) {
     Timer* tm = cfg.tm;
     const Plan& P = X.P;
@@ -1184,9 +1198,9 @@ int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg,
         // fork: every variant's launch starts after the prepass, concurrently;
         // the first runs on the batch stream itself (one hardware queue fewer
         // to share with the side streams)
-        if ((rc = ws.ensure_streams()) != MPG_OK) return rc;
-        if (hipEventRecord(ws.fork_ev, st) != hipSuccess) return MPG_E_DEVICE;
         const int ng = (int)std::min<size_t>(ngroups - 1, kSideStreams);
+        if ((rc = ws.ensure_streams(ng)) != MPG_OK) return rc;
+        if (hipEventRecord(ws.fork_ev, st) != hipSuccess) return MPG_E_DEVICE;
         for (int k = 0; k < ng; ++k)
             if (hipStreamWaitEvent(ws.side[k], ws.fork_ev, 0) != hipSuccess) return MPG_E_DEVICE;
         if (launch_group(st, 0) != hipSuccess) return MPG_E_DEVICE;
@@ -2954,6 +2968,10 @@ int mpg_plan_create(mpg_ctx* ctx, const mpg_params* p, const uint8_t* d_prot,
     for (int32_t k = 0; k < n; ++k) idx[k] = k;
     rc = prepare(ctx->stream, pl->ws, p, d_prot, d_dna, segs, idx.data(), n, ops_off, d_out,
                  d_ops, pl->cfg, pl->X);
+    // the launches' side streams now: a launch may be captured
+    const size_t ng = pl->X.P.groups.size();
+    if (rc == MPG_OK && ng > 1)
+        rc = pl->ws.ensure_streams((int)std::min<size_t>(ng - 1, kSideStreams));
     if (rc == MPG_OK && hipStreamSynchronize(ctx->stream) != hipSuccess) rc = MPG_E_DEVICE;
     if (rc != MPG_OK) {
         pl->ws.release();
@@ -2969,7 +2987,7 @@ int mpg_plan_launch(mpg_plan* plan, void* hip_stream) {
     hipSetDevice(plan->ctx->device);
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : plan->ctx->stream;
     if (plan->exec) return hipGraphLaunch(plan->exec, st) == hipSuccess ? MPG_OK : MPG_E_DEVICE;
-    return enqueue(st, plan->ws, plan->X, plan->cfg, false);
+    return enqueue(st, plan->ws, plan->X, plan->cfg, true);
 }
 
 int mpg_plan_graph(mpg_plan* plan, void* hip_stream) {
@@ -2979,7 +2997,7 @@ int mpg_plan_graph(mpg_plan* plan, void* hip_stream) {
     hipStream_t st = (hipStream_t)hip_stream;
     if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return MPG_E_DEVICE;
-    const int rc = enqueue(st, plan->ws, plan->X, plan->cfg, false);
+    const int rc = enqueue(st, plan->ws, plan->X, plan->cfg, true);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(st, &g);
     if (rc != MPG_OK || e != hipSuccess || !g) {
