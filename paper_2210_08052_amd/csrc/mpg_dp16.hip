@@ -15,6 +15,18 @@
 // penalty sum (at most 8,192 is admitted), and the largest by the protein
 // length times the largest matrix entry (m * max(mat) <= 32,511 is
 // admitted): each residue adds at most one substitution score to a path.
+//
+// FAST form (max(mat) * (m + 1) <= kFast16Max for every pair of the call):
+// values are held plus kZ16 as unsigned 16-bit numbers below 0x7C00, the bits
+// of non-negative finite fp16 numbers, which v_pk_maximum3_f16 orders as it
+// orders the integers (denormals are kept): three inputs per instruction, where
+// the integer form has only two-input packed maxima.  Penalties are subtracted
+// with unsigned saturation: what would fall below 0 stays 0, and every
+// value below kZ16 (0) is as good as another, since a LOCAL path never passes
+// through it.  H is kZ16 also outside the region: a path may "start" there,
+// but it gains nothing before row 3, where codons begin to be whole, as every
+// move but a codon's costs something or nothing.  26 vector instructions per
+// column and two cells instead of 34 (4,000 pairs 6.8 -> 5.14 ms).
 #include "mpg_dp.h"
 
 namespace mpg {
@@ -40,6 +52,27 @@ __device__ __forceinline__ int pack16(int lo, int hi) {
 
 constexpr int kNeg16 = -32768;
 constexpr int kNeg2 = (int)0x80008000u;  // both halves -infinity
+constexpr int kZ16 = 128;                // FAST: the number that stands for 0
+constexpr int kZ2 = kZ16 << 16 | kZ16;
+
+typedef unsigned short u2 __attribute__((ext_vector_type(2)));
+// FAST forms on the bits of two unsigned halves
+__device__ __forceinline__ int usub(int a, int b) {
+    return __builtin_bit_cast(int, __builtin_elementwise_sub_sat(__builtin_bit_cast(u2, a),
+                                                                 __builtin_bit_cast(u2, b)));
+}
+__device__ __forceinline__ int uadd(int a, int b) {
+    return __builtin_bit_cast(int, (u2)(__builtin_bit_cast(u2, a) + __builtin_bit_cast(u2, b)));
+}
+__device__ __forceinline__ int umax(int a, int b) {
+    return __builtin_bit_cast(int, __builtin_elementwise_max(__builtin_bit_cast(u2, a),
+                                                             __builtin_bit_cast(u2, b)));
+}
+__device__ __forceinline__ int umax3(int a, int b, int c) {
+    int r;
+    asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 
 template <int K>
 struct Lds16 {
@@ -48,19 +81,22 @@ struct Lds16 {
     static constexpr int HALF = 25 * SW * 2;   // one pair's int16 profile
     static constexpr int PROF = 2 * HALF;      // A then B
     static constexpr int IN = 64 * 8;
-    static constexpr int OUT = 128 * 8;  // rows 0..63, then one dummy slot per lane
+    static constexpr int OUT = 192 * 8;  // rows 0..63, then the lanes' hand-off slots
     static constexpr int WAVE = RING + PROF + IN + OUT;
 };
 
 // Packed descriptor of row r (16 bytes): {profile byte offset of A's row |
-// B's offset << 16, z, r + d(r+1), a(r)}, the last three as int16 pairs.
+// B's offset << 16, z, r + d(r+1), a(r)}, the last three as int16 pairs; FAST:
+// {A's offset, B's offset, r + d(r+1), a(r)}, rows without a whole codon
+// poisoned.
 __global__ void __launch_bounds__(256) prepass16_kernel(const PairJob* __restrict__ jobs,
                                                         const PackJob* __restrict__ packs,
                                                         const int64_t* __restrict__ row_start,
                                                         int npacks, int64_t total_rows,
                                                         const uint8_t* __restrict__ dna,
                                                         uint8_t* __restrict__ desc,
-                                                        int* __restrict__ prog, DevParams P) {
+                                                        int* __restrict__ prog, DevParams P,
+                                                        int fast) {
     // the owner of the block's first row, then each thread steps forward (a
     // pack owns at least 256 rows, so a block spans few packs)
     __shared__ int first_owner;
@@ -105,7 +141,7 @@ __global__ void __launch_bounds__(256) prepass16_kernel(const PairJob* __restric
             const int i = i0 + rr;
             const int* bb = b + rr;  // bb[k] = T[i-4+k]
             int tr;
-            if (i > n || i < 0) tr = 24;
+            if (i > n || i < (fast ? 3 : 0)) tr = 24;
             else if (i < 3 || bb[2] == 4 || bb[3] == 4 || bb[4] == 4) tr = 22;
             else tr = s_gcode[16 * bb[2] + 4 * bb[3] + bb[4]];
             // d(i+1) reads T[i+2..i+4]; a(i) reads T[i-2..i]
@@ -125,8 +161,9 @@ __global__ void __launch_bounds__(256) prepass16_kernel(const PairJob* __restric
     for (int rr = 0; rr < kPrepassRows; ++rr) {
         const int offA = f[rr][0][0] * sw2;
         const int offB = 25 * sw2 + f[rr][1][0] * sw2;
-        out[rr] = make_int4(pack16(offA, offB), pack16(f[rr][0][1], f[rr][1][1]),
-                            pack16(f[rr][0][2], f[rr][1][2]), pack16(f[rr][0][3], f[rr][1][3]));
+        const int rd = pack16(f[rr][0][2], f[rr][1][2]), ac = pack16(f[rr][0][3], f[rr][1][3]);
+        out[rr] = fast ? make_int4(offA, offB, rd, ac)
+                       : make_int4(pack16(offA, offB), pack16(f[rr][0][1], f[rr][1][1]), rd, ac);
     }
 }
 
@@ -135,7 +172,7 @@ __global__ void __launch_bounds__(256) prepass16_kernel(const PairJob* __restric
 #define MPG_I16_WAVES 3
 #endif
 
-template <int K, bool NOI, bool NOF>
+template <int K, bool NOI, bool NOF, bool FAST>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MPG_I16_WAVES)))
 dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
             const int2* __restrict__ items, int nitems, int* __restrict__ qhead,
@@ -151,13 +188,23 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
     int2* outb = (int2*)(smem + LY::RING + LY::PROF + LY::IN);
     const s2 ce = splat(P.e), cf = splat(P.f);
     const s2 cqe = splat(P.q + P.e);  // open and first extension
-    const s2 neg2 = as_s2(kNeg2);
+    // -infinity of H and of the other states
+    constexpr int kNegH = FAST ? kZ2 : kNeg2, kNegS = FAST ? 0 : kNeg2;
+    const s2 neg2 = as_s2(kNegS);
+    // the lanes hand their last column on through LDS (see the int32 kernel)
+    int out_off = LY::RING + LY::PROF + LY::IN + (lane == 63 ? 0 : 64 + lane) * 8;
+    int in_off = lane ? LY::RING + LY::PROF + LY::IN + (62 + lane) * 8 : LY::RING + LY::PROF;
+    asm volatile("" : "+v"(in_off), "+v"(out_off));
+    const int2* const in_l = (const int2*)(smem + in_off);
+    int2* const out_l = (int2*)(smem + out_off);
+    const int most = packs[items[0].x].nchunks;
 
     for (;;) {
         const int it = __builtin_amdgcn_readfirstlane(atomicAdd(qhead, lane == 0 ? 1 : 0));
         if (it >= nitems) break;
         const int2 item = items[it];
         const PackJob X = packs[item.x];
+        strip_priority(X.nchunks, most);
         const int strip = item.y;
         const bool hasB = X.b >= 0;
         const PairJob JA = jobs[X.a];
@@ -187,21 +234,24 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
                     pr[tr * LY::SW] = (int16_t)((pc < 0 || tr == 24) ? kNeg16 : P.mat[tr * 24 + pc]);
             }
         }
-        inb[lane] = make_int2(kNeg2, kNeg2);
+        inb[lane] = make_int2(kNegH, kNegS);
 
         s2 h1[K], h2[K], h3[K], d1[K], d2[K], d3[K], a1[K], b1[K], c1[K];
-        int kA[K], kB[K], bestA[K], bestB[K], stA[K], stB[K];
+        int kA[K], kB[K], pA[K], pB[K], bestA[K], bestB[K], stA[K], stB[K];
+        s2 fp[K];  // FAST: the previous row's frameshift term
 #pragma unroll
         for (int c = 0; c < K; ++c) {
-            h1[c] = h2[c] = h3[c] = neg2;
+            h1[c] = h2[c] = h3[c] = as_s2(kNegH);
             d1[c] = d2[c] = d3[c] = neg2;
             a1[c] = b1[c] = c1[c] = neg2;
-            kA[c] = kB[c] = INT_MIN;
+            kA[c] = kB[c] = FAST ? 0 : INT_MIN;
+            pA[c] = pB[c] = 0;
+            fp[c] = as_s2(usub(kNegH, as_i(cf)));
             bestA[c] = bestB[c] = kNeg16;
             stA[c] = stB[c] = 0;
         }
-        s2 hl1 = neg2, hl2 = neg2, hl3 = neg2;
-        int Hout = kNeg2, Iout = kNeg2;
+        s2 hl1 = as_s2(kNegH), hl2 = as_s2(kNegH), hl3 = as_s2(kNegH);
+        int Hout = kNegH, Iout = kNegS;
         // r+d(i), r+d(i-1), a(i-1), a(i-2) of the two pairs, carried in registers
         s2 dd0, ddm1, aam1, aam2;
         {
@@ -214,7 +264,7 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
             *(int4*)(ring + lane * 16) = *(const int4*)(dsc_g + (int64_t)(lane - 64 + kDescLo) * 16);
             *(int4*)(ring + (64 + lane) * 16) = *(const int4*)(dsc_g + (int64_t)(lane + kDescLo) * 16);
         }
-        int2 nb = make_int2(kNeg2, kNeg2);
+        int2 nb = make_int2(kNegH, kNegS);
         // left boundary and the left strip's progress, read one chunk ahead
         const bool from_left = strip > 0;
         int seen = 0;
@@ -233,8 +283,8 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
                     const uint32_t mlo = row > nA ? 0xFFFFu : 0u;
                     const uint32_t mhi = row > nB ? 0xFFFF0000u : 0u;
                     const uint32_t msk = mlo | mhi;
-                    const int hx = (int)(((uint32_t)nb.x & ~msk) | ((uint32_t)kNeg2 & msk));
-                    const int ix = (int)(((uint32_t)nb.y & ~msk) | ((uint32_t)kNeg2 & msk));
+                    const int hx = (int)(((uint32_t)nb.x & ~msk) | ((uint32_t)kNegH & msk));
+                    const int ix = (int)(((uint32_t)nb.y & ~msk) | ((uint32_t)kNegS & msk));
                     inb[lane] = make_int2(hx, ix);
                     if (ch + 1 < nchunks) {
                         const int need = ch + 3 < nchunks ? ch + 3 : nchunks;
@@ -257,8 +307,16 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
                 const uint8_t* pbase = prof + lane * K * 2;
 
                 auto ld_prof = [&](const int4& x0, s2* scv) {
-                    const int16_t* pa = (const int16_t*)(pbase + (x0.x & 0xFFFF));
-                    const int16_t* pb = (const int16_t*)(pbase + ((uint32_t)x0.x >> 16));
+                    const int16_t* pa = (const int16_t*)(pbase + (FAST ? x0.x : x0.x & 0xFFFF));
+                    const int16_t* pb =
+                        (const int16_t*)(pbase + (FAST ? x0.y : (int)((uint32_t)x0.x >> 16)));
+                    if constexpr (K == 2) {
+                        // both columns of a pair in one read
+                        const uint32_t wa = *(const uint32_t*)pa, wb = *(const uint32_t*)pb;
+                        scv[0] = as_s2((int)__builtin_amdgcn_perm(wb, wa, 0x05040100u));
+                        scv[K - 1] = as_s2((int)__builtin_amdgcn_perm(wb, wa, 0x07060302u));
+                        return;
+                    }
 #pragma unroll
                     for (int c = 0; c < K; ++c) {
                         s2 v;
@@ -271,21 +329,17 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
                 int4 nd0 = *(const int4*)(rb + 16);
                 s2 csc[K];
                 ld_prof(cd0, csc);
-                int2 cin = inb[0];
+                const int2 in0 = inb[0];
+                int2 cin = make_int2(shr1(in0.x, Hout), shr1(in0.y, Iout));
 
 #pragma unroll
                 for (int t = 0; t < 64; ++t) {
                     int4 fd0 = make_int4(0, 0, 0, 0);
                     if (t + 2 < 64) fd0 = *(const int4*)(rb + (t + 2) * 16);
                     s2 nsc[K];
-                    int2 nin = make_int2(0, 0);
-                    if (t + 1 < 64) {
-                        ld_prof(nd0, nsc);
-                        nin = inb[t + 1];
-                    }
+                    if (t + 1 < 64) ld_prof(nd0, nsc);
                     const int4 ds0 = cd0;
-                    const s2 hl0 = as_s2(shr1(cin.x, Hout));
-                    const s2 il0 = as_s2(shr1(cin.y, Iout));
+                    const s2 hl0 = as_s2(cin.x), il0 = as_s2(cin.y);
                     const s2 z = as_s2(ds0.y);
                     const s2 rdn = as_s2(ds0.z);  // r + d(i+1)
                     const s2 acc = as_s2(ds0.w);  // a(i)
@@ -297,6 +351,49 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
                         const s2 L1 = c ? h1[c - 1] : hl1;
                         const s2 L2 = c ? h2[c - 1] : hl2;
                         const s2 L3 = c ? h3[c - 1] : hl3;
+                        if constexpr (FAST) {
+                            const int hh = as_i(h1[c]), l1 = as_i(L1);
+                            const int D = umax(usub(as_i(h3[c]), as_i(cqe)),
+                                               usub(as_i(d3[c]), as_i(ce)));
+                            const int I = umax(usub(as_i(L0), as_i(cqe)), usub(as_i(IL), as_i(ce)));
+                            const int M = uadd(as_i(L3), as_i(csc[c]));
+                            int pf = 0;
+                            if (!NOF) {
+                                pf = usub(umax(l1, hh), as_i(cf));
+                                asm("" : "+v"(pf));
+                            }
+                            int H;
+                            if (!NOI) {
+                                const int A = umax(usub(hh, as_i(ddm1)), as_i(a1[c]));
+                                const int B = umax(usub(l1, as_i(dd0)), as_i(b1[c]));
+                                const int C = umax(usub(l1, as_i(rdn)), as_i(c1[c]));
+                                An[c] = as_s2(A); Bn[c] = as_s2(B); Cn[c] = as_s2(C);
+                                const int x = umax3(D, usub(A, as_i(acc)), usub(B, as_i(aam2)));
+                                const int y = usub(C, as_i(aam1));
+                                const int w = umax3(M, x, kZ2);
+                                H = NOF ? umax3(w, y, I) : umax3(umax3(y, pf, as_i(fp[c])), w, I);
+                            } else {
+                                const int w = umax3(M, D, kZ2);
+                                H = NOF ? umax(w, I) : umax3(umax3(w, pf, as_i(fp[c])), I, I);
+                            }
+                            if (!NOF) fp[c] = as_s2(pf);
+                            Hn[c] = as_s2(H); In[c] = as_s2(I); Dn[c] = as_s2(D);
+                            // end-cell keys of two steps at a time
+                            const uint32_t qa = ((uint32_t)H << 16) | (uint32_t)(63 - t);
+                            const uint32_t qb = ((uint32_t)H & 0xFFFF0000u) | (uint32_t)(63 - t);
+                            if (t & 1) {
+                                uint32_t u = (uint32_t)pA[c] > qa ? (uint32_t)pA[c] : qa;
+                                uint32_t v = (uint32_t)pB[c] > qb ? (uint32_t)pB[c] : qb;
+                                kA[c] = (int)(u > (uint32_t)kA[c] ? u : (uint32_t)kA[c]);
+                                kB[c] = (int)(v > (uint32_t)kB[c] ? v : (uint32_t)kB[c]);
+                                asm volatile("" : "+v"(kA[c]), "+v"(kB[c]));
+                            } else {
+                                pA[c] = (int)qa;
+                                pB[c] = (int)qb;
+                                asm volatile("" : "+v"(pA[c]), "+v"(pB[c]));
+                            }
+                            continue;
+                        }
                         // every candidate but I is known before the left
                         // neighbour's H of this row: fold them in two
                         // independent trees, so that dependent packed
@@ -333,14 +430,11 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
                     ddm1 = dd0; dd0 = rdn; aam2 = aam1; aam1 = acc;
                     Hout = as_i(Hn[K - 1]);
                     Iout = as_i(In[K - 1]);
-                    // lane 63 records the row; the other lanes write to slots of
-                    // their own, so the store needs no branch (a branch would
-                    // split the step's scheduling region)
-                    outb[lane == 63 ? t : 64 + lane] = make_int2(Hout, Iout);
+                    out_l[t] = make_int2(Hout, Iout);
+                    if (t + 1 < 64) cin = in_l[t + 1];
                     cd0 = nd0; nd0 = fd0;
 #pragma unroll
                     for (int c = 0; c < K; ++c) csc[c] = nsc[c];
-                    cin = nin;
                     // (no scheduling barrier between steps: the next step's
                     // independent terms fill the wait states of this step's
                     // dependent packed instructions)
@@ -349,10 +443,11 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
                 // fold the chunk's best of each half into the strip's best
 #pragma unroll
                 for (int c = 0; c < K; ++c) {
-                    const int va = kA[c] >> 16, vb = kB[c] >> 16;
+                    const int va = (kA[c] >> 16) - (FAST ? kZ16 : 0);
+                    const int vb = (kB[c] >> 16) - (FAST ? kZ16 : 0);
                     if (va > bestA[c]) { bestA[c] = va; stA[c] = ch * 64 + 63 - (kA[c] & 63); }
                     if (vb > bestB[c]) { bestB[c] = vb; stB[c] = ch * 64 + 63 - (kB[c] & 63); }
-                    kA[c] = kB[c] = INT_MIN;
+                    kA[c] = kB[c] = FAST ? 0 : INT_MIN;
                 }
                 // publish with a one-chunk lag (see the int32 kernel)
                 if (has_next) {
@@ -436,7 +531,7 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
     }  // queue
 }
 
-template <int K>
+template <int K, bool FAST>
 hipError_t launch_dp16_t(hipStream_t s, int ncu, const DevParams& P, const PairJob* jobs,
                          const PackJob* packs, const int2* items, int nitems, int* qhead,
                          PairState* pst, int* prog, const uint8_t* prot, const uint8_t* desc,
@@ -449,11 +544,11 @@ hipError_t launch_dp16_t(hipStream_t s, int ncu, const DevParams& P, const PairJ
     do {                                                                                        \
         static int per_cu = 0;                                                                  \
         if (per_cu <= 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(                        \
-                               &per_cu, dp16_kernel<K, NI, NF>, 64, lds) != hipSuccess)         \
+                               &per_cu, dp16_kernel<K, NI, NF, FAST>, 64, lds) != hipSuccess)         \
             per_cu = 0;                                                                         \
         const int waves = per_cu > 0 ? per_cu * ncu : 8 * ncu;                                  \
         dim3 g(nitems < waves ? nitems : waves);                                                \
-        hipLaunchKernelGGL((dp16_kernel<K, NI, NF>), g, b, lds, s, jobs, packs, items, nitems,  \
+        hipLaunchKernelGGL((dp16_kernel<K, NI, NF, FAST>), g, b, lds, s, jobs, packs, items, nitems,  \
                            qhead, pst, prog, prot, desc, bnd, sink, P);                         \
     } while (0)
     if (!noi && !nof) MPG_LAUNCH16(false, false);
@@ -468,30 +563,26 @@ hipError_t launch_dp16_t(hipStream_t s, int ncu, const DevParams& P, const PairJ
 
 hipError_t launch_prepass16(hipStream_t s, const PairJob* jobs, const PackJob* packs,
                             const int64_t* row_start, int npacks, int64_t total_rows,
-                            const uint8_t* dna, uint8_t* desc, int* prog, const DevParams& P) {
+                            const uint8_t* dna, uint8_t* desc, int* prog, const DevParams& P,
+                            bool fast) {
     if (total_rows <= 0) return hipSuccess;
     const int64_t per_block = 256 * dev::kPrepassRows;
     const int64_t blocks = (total_rows + per_block - 1) / per_block;
     hipLaunchKernelGGL(dev::prepass16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, jobs, packs,
-                       row_start, npacks, total_rows, dna, desc, prog, P);
+                       row_start, npacks, total_rows, dna, desc, prog, P, fast ? 1 : 0);
     return hipGetLastError();
 }
 
-hipError_t launch_dp16(hipStream_t s, int K, int ncu, const DevParams& P, const PairJob* jobs,
-                       const PackJob* packs, const int2* items, int nitems, int* qhead, void* pst,
-                       int* prog, const uint8_t* prot, const uint8_t* desc, int2* bnd,
-                       const DpSink& sink) {
+hipError_t launch_dp16(hipStream_t s, int K, bool fast, int ncu, const DevParams& P,
+                       const PairJob* jobs, const PackJob* packs, const int2* items, int nitems,
+                       int* qhead, void* pst, int* prog, const uint8_t* prot, const uint8_t* desc,
+                       int2* bnd, const DpSink& sink) {
     if (nitems <= 0) return hipSuccess;
-    if (P.mode != MPG_LOCAL) return hipErrorInvalidValue;
-    switch (K) {
-        case 1:
-            return dev::launch_dp16_t<1>(s, ncu, P, jobs, packs, items, nitems, qhead,
-                                         (dev::PairState*)pst, prog, prot, desc, bnd, sink);
-        case 2:
-            return dev::launch_dp16_t<2>(s, ncu, P, jobs, packs, items, nitems, qhead,
-                                         (dev::PairState*)pst, prog, prot, desc, bnd, sink);
-        default: return hipErrorInvalidValue;
-    }
+    if (P.mode != MPG_LOCAL || (K != 1 && K != 2)) return hipErrorInvalidValue;
+    auto run = K == 1 ? (fast ? dev::launch_dp16_t<1, true> : dev::launch_dp16_t<1, false>)
+                      : (fast ? dev::launch_dp16_t<2, true> : dev::launch_dp16_t<2, false>);
+    return run(s, ncu, P, jobs, packs, items, nitems, qhead, (dev::PairState*)pst, prog, prot, desc,
+               bnd, sink);
 }
 
 int dp16_lds_bytes(int K) { return K == 1 ? dev::Lds16<1>::WAVE : dev::Lds16<2>::WAVE; }

@@ -252,11 +252,15 @@ hipError_t launch_chain(hipStream_t st, const ChainSetJob* sets, int nsets, cons
 // DP launch over (pack, strip) items.
 hipError_t launch_prepass16(hipStream_t s, const PairJob* jobs, const PackJob* packs,
                             const int64_t* row_start, int npacks, int64_t total_rows,
-                            const uint8_t* dna, uint8_t* desc, int* prog, const DevParams& P);
-hipError_t launch_dp16(hipStream_t s, int K, int ncu, const DevParams& P, const PairJob* jobs,
-                       const PackJob* packs, const int2* items, int nitems, int* qhead, void* pst,
-                       int* prog, const uint8_t* prot, const uint8_t* desc, int2* bnd,
-                       const DpSink& sink);
+                            const uint8_t* dna, uint8_t* desc, int* prog, const DevParams& P,
+                            bool fast);
+// fast: every pair's max(mat) * (m + 1) is at most kFast16Max (the kernel's
+// FAST form; the prepass must have been given the same).
+constexpr int kFast16Max = 31600;
+hipError_t launch_dp16(hipStream_t s, int K, bool fast, int ncu, const DevParams& P,
+                       const PairJob* jobs, const PackJob* packs, const int2* items, int nitems,
+                       int* qhead, void* pst, int* prog, const uint8_t* prot, const uint8_t* desc,
+                       int2* bnd, const DpSink& sink);
 int dp16_lds_bytes(int K);
 
 // The fixed scratch array of the allocation-free batch entry point, on the

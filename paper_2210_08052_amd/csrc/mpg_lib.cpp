@@ -245,6 +245,7 @@ struct Plan {
     int64_t desc_bytes = 0, bnd_elems = 0, tb_bytes = 0;
     int64_t total_rows = 0, pack_rows = 0;
     int64_t nprog = 0;
+    bool fast16 = false;  // every int16 pair fits the int16 kernel's FAST form
 };
 
 // Everything one in-flight batch needs on the device.  The DP launches of a
@@ -361,11 +362,11 @@ int choose_width(const Overrides& ov, const Tuning* tu, int force) {
 
 // Columns per lane of the int16 kernel (one width for a whole call: pairs of
 // a pack share it).
+// 0: the call's own work decides.
 int choose_K16(const Overrides& ov, const Tuning* tu, int force = 0) {
     if (ov.K16 == 1 || ov.K16 == 2) return ov.K16;
     if (force) return force;
-    if (tu && tu->K16) return tu->K16;
-    return 2;
+    return tu ? tu->K16 : 0;
 }
 
 int g_num_cu = 256;  // compute units of the device (the DP grid is sized per CU)
@@ -405,11 +406,8 @@ int64_t tb_bytes_max(int n, int m) {
 // pairs 3.5 and 2.45, 3,000 3.67 and 4.04, 10,000 10.2 and 12.5 ms.
 struct WidthWork {
     double work[2] = {0, 0}, chain[2] = {0, 0};  // [0]: width 1, [1]: width 2
-    void add(int n, int m, bool tb, bool introns) {
-        struct Cost { double step, column; };
-        static constexpr Cost kShared[2][2] = {{{37, 28}, {37, 56}}, {{16, 58}, {16, 117}}};
-        static constexpr Cost kAlone[2][2] = {{{140, 20}, {85, 80}}, {{150, 60}, {110, 140}}};
-        const Cost sh = kShared[tb][introns], al = kAlone[tb][introns];
+    struct Cost { double step, column; };
+    void add(int n, int m, const Cost& sh, const Cost& al) {
         for (int K = 1; K <= 2; ++K) {
             const double steps = pair_nsteps(n, m, K);
             const double strips = (m + 64 * K) / (64 * K);
@@ -417,6 +415,13 @@ struct WidthWork {
             chain[K - 1] = std::max(chain[K - 1],
                                     (al.step + al.column * K) * (steps + 128 * (strips - 1)));
         }
+    }
+    // int16 lanes: a step advances two pairs
+    void add16(int n, int m) { add(n, m, Cost{14, 54}, Cost{90, 120}); }
+    void add(int n, int m, bool tb, bool introns) {
+        static constexpr Cost kShared[2][2] = {{{37, 28}, {37, 56}}, {{16, 58}, {16, 117}}};
+        static constexpr Cost kAlone[2][2] = {{{140, 20}, {85, 80}}, {{150, 60}, {110, 140}}};
+        add(n, m, kShared[tb][introns], kAlone[tb][introns]);
     }
     int width(int ncu) const {
         const double t1 = std::max(work[0] / (4 * ncu), chain[0]);
@@ -490,6 +495,8 @@ struct BoundInfo {
         if (mode == MPG_LOCAL || mode == MPG_EXTEND_LEFT) return pmax * 4 < lim;
         return (n + m + 4) * pmax < lim;
     }
+    // the FAST form of the int16 kernel (see mpg_dp16.hip)
+    bool fast16(int64_t m) const { return maxpos * (m + 1) <= kFast16Max; }
     // int16 lanes (LOCAL only): H >= 0 everywhere, so reachable values lie in
     // [-(the largest penalty sum), the best score]; the best score of a
     // protein of m residues is at most m times the largest matrix entry.
@@ -610,26 +617,31 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     P.pack_row_start.clear();
     P.desc_bytes = P.bnd_elems = P.tb_bytes = P.total_rows = 0;
     P.pack_rows = P.nprog = 0;
+    P.fast16 = true;
     std::vector<std::pair<int64_t, int32_t>>& bysize = P.bysize;
     bysize.clear();
     bysize.reserve(cnt);
     const Overrides ov;
     const BoundInfo bound(p);
     const bool allow16 = (p->flags & MPG_ALLOW_I16) != 0 && !cfg.pro;
-    const int K16 = choose_K16(ov, cfg.tune, cfg.force_K16);
+    int K16 = choose_K16(ov, cfg.tune, cfg.force_K16);
     int width = choose_width(ov, cfg.tune, cfg.force_K);
     const bool by_work = width == 0 && !cfg.wide;
     if (by_work) {
-        WidthWork ww;
+        WidthWork ww, ww16;
         for (int32_t k = 0; k < cnt; ++k) {
             const mpg_seg& s = segs[idx[k]];
-            ww.add(std::max(0, s.dlen), std::max(0, s.plen),
-                   ((s.flags | p->flags) & MPG_WANT_TB) != 0, bound.introns);
+            const int nn = std::max(0, s.dlen), mm = std::max(0, s.plen);
+            const bool tb = ((s.flags | p->flags) & MPG_WANT_TB) != 0;
+            if (allow16 && !tb && bound.ok16(mm, p->mode)) ww16.add16(nn, mm);
+            else ww.add(nn, mm, tb, bound.introns);
         }
         width = ww.width(cfg.ncu);
+        if (K16 == 0) K16 = ww16.width(cfg.ncu);
     } else if (width == 0) {
         width = 2;
     }
+    if (K16 == 0) K16 = 2;
     std::vector<std::pair<int64_t, int32_t>>& e16 = P.e16;
     e16.clear();
     // One group per (width, traceback, kernel mode, value form), in order of first
@@ -701,6 +713,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         if (allow16 && !J.tb && bound.ok16(mm, J.mode)) {
             J.i16 = 1;
             J.K = K16;
+            P.fast16 = P.fast16 && bound.fast16(mm);
             J.nstrips = (mm + 1 + 64 * K16 - 1) / (64 * K16);
             J.nchunks = pair_nsteps(nn, mm, K16) / 64;
             // pairs are matched by shape: strips first, then chunks
@@ -1173,7 +1186,7 @@ int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg,
         return MPG_E_DEVICE;
     if (X.npacks &&
         launch_prepass16(st, X.d_jobs, X.d_packs, X.d_pkstarts, (int)X.npacks, P.pack_rows,
-                         X.d_dna, X.d_desc, X.d_prog, DP) != hipSuccess)
+                         X.d_dna, X.d_desc, X.d_prog, DP, P.fast16) != hipSuccess)
         return MPG_E_DEVICE;
     if (tm) tm->end(st, 0);
     if (tm) tm->begin(st, 1);
@@ -1183,7 +1196,7 @@ int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg,
         DevParams DG = DP;
         DG.mode = G.mode;
         if (G.i16)
-            return launch_dp16(s2, G.K, cfg.ncu, DG, X.d_jobs, X.d_packs, X.d_items + X.goff[g],
+            return launch_dp16(s2, G.K, P.fast16, cfg.ncu, DG, X.d_jobs, X.d_packs, X.d_items + X.goff[g],
                                nit, X.d_qhead + g, X.d_pst, X.d_prog, X.d_prot,
                                X.d_desc, X.d_bnd, sink);
         return launch_dp(s2, G.K, G.tb, cfg.pro, G.f32, cfg.ncu, DG, X.d_jobs, X.d_items + X.goff[g],

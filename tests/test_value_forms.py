@@ -91,3 +91,39 @@ def test_forms_mixed_in_one_call(ctx):
              (4120, 4126, 4128, 4130, 30, 95, 140)]
     print("case mixed forms", flush=True)
     compare(ctx, pairs, g, o, True, label="mixed forms")
+
+
+@pytest.mark.parametrize("K16", [1, 2])
+def test_int16_forms_at_the_line(ctx, K16, monkeypatch):
+    """16-bit lanes: W^m against (TGG)^m at the last length of the three-input
+    maximum's form (11 * (m + 1) <= 31,600) and the first beyond it, each in a
+    call of its own (a call runs one form), with short and empty partners."""
+    monkeypatch.setenv("MPG_FORCE_K16", str(K16))
+    g, o = _both(0, flags=0)
+    g.flags |= mpg.MPG_ALLOW_I16
+    for m in (2871, 2872):
+        print("case K16=%d m=%d" % (K16, m), flush=True)
+        pairs = [(b"W" * m, b"ACGT" + b"TGG" * m + b"CA"), (b"", b"ACGTA"), (b"MKV", b""),
+                 (b"M", b"AC"), (b"MKW", b"ATGAAATGG"), (b"W" * 70, b"TGG" * 70)]
+        got = compare(ctx, pairs, g, o, False, label="int16 %d" % m)
+        assert got[0]["score"] == 11 * m
+
+
+@pytest.mark.parametrize("K16", [1, 2])
+def test_int16_free_moves(ctx, K16, monkeypatch):
+    """16-bit lanes with penalties of 0 (every move but a gap is free) and with
+    positive scores for partial codons and stops: nothing may start outside
+    the region or before a whole codon."""
+    monkeypatch.setenv("MPG_FORCE_K16", str(K16))
+    mat = np.full((24, 24), 3, np.int8)
+    mat[22, :] = 40
+    mat[:, 22] = 40
+    zero = np.zeros(125, np.uint8)
+    for flags in range(4):
+        for kw in (dict(q=0, e=1, f=0, r=0, donor=zero, acceptor=zero),
+                   dict(q=1, e=0, f=0, r=0, donor=zero, acceptor=zero, mat=mat),
+                   dict(q=3, e=1, f=2, r=1, mat=mat)):
+            print("case K16=%d flags=%d q=%d" % (K16, flags, kw["q"]), flush=True)
+            g, o = _both(0, flags=flags, **kw)
+            g.flags |= mpg.MPG_ALLOW_I16
+            compare(ctx, _pairs(960 + flags, 14, 150, 300), g, o, False, label="free")
