@@ -377,10 +377,12 @@ int64_t mpg_chain_ops_capacity(const mpg_params *p, const mpg_chain_seg *chains,
  * receive the results; each record's ops_off locates its op string.  The
  * device buffers must stay valid until the stream has finished; the anchors
  * are read before the call returns.  MPG_E_RANGE if ops_cap is too small.
- * A call of 2,048 chains or more runs in two halves on two workspaces of its
+ * A call of 512 chains or more runs in two halves on two workspaces of its
  * own: the host plans the second half while the device runs the first, and
  * waits only for the previous call's use of each workspace, not for the whole
- * stream.  Every chain is checked before any work is enqueued. */
+ * stream.  The second half runs on a stream of the context's, forked from and
+ * joined to the context's stream.  Every chain is checked before any work is
+ * enqueued. */
 int mpg_align_chains_dev(mpg_ctx *ctx, const mpg_params *p, const uint8_t *d_prot,
                          const uint8_t *d_dna, const mpg_chain_seg *chains, int32_t n,
                          mpg_dev_result *d_out, char *d_ops, int64_t ops_cap);
@@ -560,7 +562,8 @@ int mpg_get_stats(mpg_ctx *ctx, mpg_stats *st);
 
 /* Cumulative device time of the batch calls of this context, measured with
  * hipEvents on the context's stream around the prepass kernel, the DP kernels
- * and the traceback walk (only while timing is enabled). */
+ * and the traceback walk (only while timing is enabled).  The halves of a
+ * large anchor-driven call overlap, and each counts its own time. */
 typedef struct {
     double prepass_ms, dp_ms, walk_ms;
     uint64_t dp_spans; /* number of timed DP spans (one per batch wave) */

@@ -823,10 +823,12 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
     // a select in packed strips; this read takes the place of the broadcast
     // read of the boundary row, and the step's other terms cover its latency.
     // One base per lane, the step in the immediate offset.  Without introns
-    // there are too few other terms (27 instructions per step): a call that
-    // leaves the device idle waits for the hand-off, so those kernels shift by
-    // DPP (rescoring 800 pairs 1.21 -> 1.05 ms).
-    constexpr bool XLDS = !NOI;
+    // or at one column without traceback there are too few other terms (25
+    // instructions per step): a call that leaves the device idle waits for the
+    // hand-off, so those kernels shift by DPP (rescoring 800 pairs 1.21 ->
+    // 1.05 ms, 1,000 profiles 2.55 -> 2.41; one column with traceback gains 2%
+    // alone and loses 7% on 1,500 pairs).
+    constexpr bool XLDS = !NOI && (K > 1 || TB);
     int out_off = LY::RING + LY::PROF + LY::IN + (lane == 63 ? 0 : 64 + lane) * 8;
     int in_off = lane ? LY::RING + LY::PROF + LY::IN + (62 + lane) * 8 : LY::RING + LY::PROF;
     asm volatile("" : "+v"(in_off), "+v"(out_off));
@@ -1164,6 +1166,10 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
 #pragma unroll
                         for (int c = 0; c < K; ++c) {
                             const int v = take ? Hn[c] : NEG;
+                            if (F32) {  // one key, as in LOCAL
+                                key_push<TB, F32>(bk[c], kp[c], v, t);
+                                continue;
+                            }
                             const bool gt = v > bk[c];
                             bk[c] = gt ? v : bk[c];
                             bkt[c] = gt ? t : bkt[c];
@@ -1179,7 +1185,7 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                             // (about 100 more VGPRs, one wave per SIMD)
                             asm volatile("" : "+v"(hn[c]));
                         }
-                    } else if (MODE == MPG_LOCAL) {
+                    } else if (MODE == MPG_LOCAL || F32) {
 #pragma unroll
                         for (int c = 0; c < K; ++c)
                             key_push<TB, F32>(bk[c], kp[c], Hn[c], t);
@@ -1237,7 +1243,10 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
 #pragma unroll
                     for (int c = 0; c < K; ++c) {
                         int v, tt;
-                        if (MODE == MPG_LOCAL) { v = key_value<TB, F32>(bk[c]); tt = 63 - (bk[c] & 63); }
+                        if (MODE == MPG_LOCAL || F32) {
+                            v = key_value<TB, F32>(bk[c]);
+                            tt = 63 - (bk[c] & 63);
+                        }
                         else { v = bk[c]; tt = bkt[c]; }
                         if (v > best[c]) { best[c] = v; bstep[c] = ch * 64 + tt; }
                         bk[c] = kNone;
