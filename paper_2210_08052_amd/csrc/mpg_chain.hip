@@ -17,7 +17,8 @@
 // exceeds G.  Then the block's own anchors are settled one after another, each
 // offered to the lanes behind it.  (One anchor at a time, the lanes striding
 // over its candidates and an arg-max over the workgroup, took 3.4 us per
-// anchor of the largest set: 2.42 ms for 3,000 sets of up to 700 anchors.)
+// anchor of the largest set: 2.42 ms for 3,000 sets of up to 700 anchors; now
+// 1.07 ms.)
 //
 // f of the set's anchors lives in LDS (fp64), or, for a set too large for it,
 // in the f output in HBM, read and written with device-scope atomics so that

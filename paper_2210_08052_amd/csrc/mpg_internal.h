@@ -150,14 +150,13 @@ hipError_t launch_dp(hipStream_t s, int K, bool tb, bool pro, bool f32, int ncu,
                      int* prog, const uint8_t* prot, const uint8_t* desc, int2* bnd,
                      uint8_t* tbbuf, const DpSink& sink);
 
-// Zero the per-pair state, the strips' progress counters and the queue heads.
+// Zero the per-pair state, the strips' progress counters and the queue heads,
+// and write the records of pairs that the host rejected.
 hipError_t launch_init(hipStream_t s, const PairJob* jobs, int npairs, void* pst, int* prog,
-                       int* qheads, int nq, int gsc_init);
+                       int* qheads, int nq, int gsc_init, const DpSink& sink);
 
 hipError_t launch_walk(hipStream_t s, const PairJob* jobs, const int32_t* order, int count,
                        const uint8_t* tbbuf, mpg_dev_result* out, char* ops);
-
-hipError_t launch_status(hipStream_t s, const PairJob* jobs, int npairs, const DpSink& sink);
 
 // One chain of anchor runs (device copy; 56 bytes).  Its pieces are
 // consecutive in the piece results: the left extension, the gaps between

@@ -139,7 +139,8 @@ __global__ void __launch_bounds__(256) prepass_kernel(const PairJob* __restrict_
 
 // ------------------------------------------------------------------- init
 __global__ void init_kernel(const PairJob* __restrict__ jobs, int npairs, PairState* __restrict__ pst,
-                            int* __restrict__ prog, int* __restrict__ qheads, int nq, int gsc_init) {
+                            int* __restrict__ prog, int* __restrict__ qheads, int nq,
+                            int gsc_init, DpSink sink) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k < nq) qheads[k] = 0;
     if (k >= npairs) return;
@@ -149,7 +150,18 @@ __global__ void init_kernel(const PairJob* __restrict__ jobs, int npairs, PairSt
     pst[k].gsc = gsc_init;
     pst[k].bad = 0;
     pst[k].pad = 0;
-    if (J.status != MPG_OK || J.i16) return;
+    if (J.status != MPG_OK) {  // rejected by the host: its record
+        mpg_dev_result R;
+        R.status = J.status;
+        R.score = 0;
+        R.g_beg = R.g_end = R.p_beg = R.p_end = -1;
+        R.ops_off = J.ops_off;
+        R.ops_len = 0;
+        R._pad = 0;
+        publish(sink.out + J.res, R, sink.system);
+        return;
+    }
+    if (J.i16) return;
     for (int s = 0; s < J.nstrips; ++s) prog[J.prog_off + s] = 0;
 }
 
@@ -191,22 +203,6 @@ __global__ void __launch_bounds__(64) walk_kernel(const PairJob* __restrict__ jo
         }
         out[J.res] = R;
     }
-}
-
-// Records for pairs the host rejected before launch.
-__global__ void status_kernel(const PairJob* __restrict__ jobs, int npairs, DpSink sink) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= npairs) return;
-    const PairJob J = jobs[k];
-    if (J.status == MPG_OK) return;
-    mpg_dev_result R;
-    R.status = J.status;
-    R.score = 0;
-    R.g_beg = R.g_end = R.p_beg = R.p_end = -1;
-    R.ops_off = J.ops_off;
-    R.ops_len = 0;
-    R._pad = 0;
-    publish(sink.out + J.res, R, sink.system);
 }
 
 // ------------------------------------------------------------------ stitch
@@ -502,11 +498,11 @@ hipError_t launch_dp(hipStream_t s, int K, bool tb, bool pro, bool f32, int ncu,
 }
 
 hipError_t launch_init(hipStream_t s, const PairJob* jobs, int npairs, void* pst, int* prog,
-                       int* qheads, int nq, int gsc_init) {
+                       int* qheads, int nq, int gsc_init, const DpSink& sink) {
     if (npairs <= 0 && nq <= 0) return hipSuccess;
     const int n = npairs > nq ? npairs : nq;
     hipLaunchKernelGGL(init_kernel, dim3((n + 255) / 256), dim3(256), 0, s, jobs, npairs,
-                       (PairState*)pst, prog, qheads, nq, gsc_init);
+                       (PairState*)pst, prog, qheads, nq, gsc_init, sink);
     return hipGetLastError();
 }
 
@@ -541,13 +537,6 @@ hipError_t launch_rescore_finish(hipStream_t s, int n, const mpg_dev_result* res
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(rescore_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, res1,
                        info, j2, res2, r, score, exons, status);
-    return hipGetLastError();
-}
-
-hipError_t launch_status(hipStream_t s, const PairJob* jobs, int npairs, const DpSink& sink) {
-    if (npairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(status_kernel, dim3((npairs + 255) / 256), dim3(256), 0, s, jobs, npairs,
-                       sink);
     return hipGetLastError();
 }
 

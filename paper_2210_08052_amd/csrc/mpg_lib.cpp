@@ -253,7 +253,7 @@ struct Plan {
 // from the batch stream and joined back with events.
 constexpr int kSideStreams = 8;
 struct Workspace {
-    DevBuf jobs, row_start, order, desc, bnd, tb, seq, out, ops, state, chain, piece_out,
+    DevBuf jobs, desc, bnd, tb, seq, out, ops, state, chain, piece_out,
         piece_ops, cset, cio;
     HostBuf hplan, hseq, hout, hops, hchain, hcset;
     HostBuf prec, pops;  // serving: host-mapped records and op strings the host polls
@@ -267,12 +267,12 @@ struct Workspace {
     std::vector<int64_t> wave_ops_off;
     std::vector<int32_t> wave_idx;
     void use_allocator(const DevAlloc* a) {
-        DevBuf* d[] = {&jobs, &row_start, &order, &desc, &bnd, &tb, &seq, &out, &ops, &state,
+        DevBuf* d[] = {&jobs, &desc, &bnd, &tb, &seq, &out, &ops, &state,
                        &chain, &piece_out, &piece_ops, &cset, &cio};
         for (auto* b : d) b->src = a;
     }
     void defer_frees(Retired* r) {
-        DevBuf* d[] = {&jobs, &row_start, &order, &desc, &bnd, &tb, &seq, &out, &ops, &state,
+        DevBuf* d[] = {&jobs, &desc, &bnd, &tb, &seq, &out, &ops, &state,
                        &chain, &piece_out, &piece_ops, &cset, &cio};
         for (auto* b : d) b->later = r;
         HostBuf* h[] = {&hplan, &hseq, &hout, &hops, &prec, &pops, &hchain, &hcset};
@@ -301,7 +301,7 @@ struct Workspace {
         return MPG_OK;
     }
     void release() {
-        DevBuf* d[] = {&jobs, &row_start, &order, &desc, &bnd, &tb, &seq, &out, &ops, &state,
+        DevBuf* d[] = {&jobs, &desc, &bnd, &tb, &seq, &out, &ops, &state,
                        &chain, &piece_out, &piece_ops, &cset, &cio};
         for (auto* b : d) b->release();
         HostBuf* h[] = {&hplan, &hseq, &hout, &hops, &prec, &pops, &hchain, &hcset};
@@ -1087,15 +1087,15 @@ int prepare(hipStream_t st, Workspace& ws, const mpg_params* p, const uint8_t* d
     const auto tw0 = std::chrono::steady_clock::now();
     if ((rc = wait_workspace(st, cfg)) != MPG_OK) return rc;
     host_clock.t0 += std::chrono::steady_clock::now() - tw0;
-    const size_t b_jobs = jobs_b + pj_b + pk_b + 256, b_rs = ps_b + pks_b + 64,
-                 b_order = it_b + wk_b + 64, b_desc = (size_t)P.desc_bytes + 64,
+    // the plan in one block, device and staging alike (so that one copy
+    // uploads it): jobs, prepass jobs, packs | row starts, pack row starts |
+    // items, walk list; each part's entries are aligned by the ones before
+    const size_t plan_b = jobs_b + pj_b + pk_b + ps_b + pks_b + it_b + wk_b;
+    const size_t b_plan = plan_b + 64, b_desc = (size_t)P.desc_bytes + 64,
                  b_bnd = sizeof(int2) * (size_t)P.bnd_elems + 64,
                  b_tb = (size_t)P.tb_bytes + 64,
                  b_state = (size_t)kPairStateBytes * cnt + sizeof(int) * (P.nprog + 64);
-    // staging layout: jobs, prepass jobs, packs | row starts, pack row
-    // starts | items, walk list
-    const size_t plan_b = jobs_b + pj_b + pk_b + ps_b + pks_b + it_b + wk_b + 1024;
-    uint8_t *p_jobs, *p_rs, *p_order, *p_desc, *p_bnd, *p_tb, *p_state;
+    uint8_t *p_jobs, *p_desc, *p_bnd, *p_tb, *p_state;
     uint8_t* h;
     if (fx) {
         size_t off = 0;
@@ -1104,9 +1104,7 @@ int prepare(hipStream_t st, Workspace& ws, const mpg_params* p, const uint8_t* d
             off += (bytes + 255) & ~(size_t)255;
             return q;
         };
-        p_jobs = carve(b_jobs);
-        p_rs = carve(b_rs);
-        p_order = carve(b_order);
+        p_jobs = carve(b_plan);
         p_desc = carve(b_desc);
         p_bnd = carve(b_bnd);
         p_tb = carve(b_tb);
@@ -1115,17 +1113,13 @@ int prepare(hipStream_t st, Workspace& ws, const mpg_params* p, const uint8_t* d
         if (fx->stage->size() < plan_b) fx->stage->resize(plan_b);
         h = fx->stage->data();
     } else {
-        if ((rc = ws.jobs.ensure(b_jobs)) != MPG_OK) return rc;
-        if ((rc = ws.row_start.ensure(b_rs)) != MPG_OK) return rc;
-        if ((rc = ws.order.ensure(b_order)) != MPG_OK) return rc;
+        if ((rc = ws.jobs.ensure(b_plan)) != MPG_OK) return rc;
         if ((rc = ws.desc.ensure(b_desc)) != MPG_OK) return rc;
         if ((rc = ws.bnd.ensure(b_bnd)) != MPG_OK) return rc;
         if ((rc = ws.tb.ensure(b_tb)) != MPG_OK) return rc;
         if ((rc = ws.state.ensure(b_state)) != MPG_OK) return rc;
         if ((rc = ws.hplan.ensure(plan_b)) != MPG_OK) return rc;
         p_jobs = (uint8_t*)ws.jobs.p;
-        p_rs = (uint8_t*)ws.row_start.p;
-        p_order = (uint8_t*)ws.order.p;
         p_desc = (uint8_t*)ws.desc.p;
         p_bnd = (uint8_t*)ws.bnd.p;
         p_tb = (uint8_t*)ws.tb.p;
@@ -1144,23 +1138,18 @@ int prepare(hipStream_t st, Workspace& ws, const mpg_params* p, const uint8_t* d
     X.d_jobs = (PairJob*)p_jobs;
     X.d_pjobs = all_int32 ? (PairJob*)p_jobs : (PairJob*)(p_jobs + jobs_b);
     X.d_packs = (PackJob*)(p_jobs + jobs_b + pj_b);
-    X.d_starts = (int64_t*)p_rs;
-    X.d_pkstarts = (int64_t*)(p_rs + ps_b);
-    X.d_items = (int2*)p_order;
-    X.d_walk = (int32_t*)(p_order + it_b);
+    X.d_starts = (int64_t*)(p_jobs + (h2 - h));
+    X.d_pkstarts = X.d_starts + X.npjobs;
+    X.d_items = (int2*)(p_jobs + (h3 - h));
+    X.d_walk = (int32_t*)((uint8_t*)X.d_items + it_b);
     X.d_desc = p_desc;
     X.d_bnd = (int2*)p_bnd;
     X.d_tb = p_tb;
     X.d_pst = p_state;
     X.d_qhead = (int*)(p_state + (size_t)kPairStateBytes * cnt);  // one per launch
     X.d_prog = X.d_qhead + 16;
-    hipError_t e = hipSuccess;
-    if (jobs_b + pj_b + pk_b)
-        e = hipMemcpyAsync(p_jobs, h, jobs_b + pj_b + pk_b, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && ps_b + pks_b)
-        e = hipMemcpyAsync(X.d_starts, h2, ps_b + pks_b, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && it_b + wk_b)
-        e = hipMemcpyAsync(p_order, h3, it_b + wk_b, hipMemcpyHostToDevice, st);
+    const hipError_t e =
+        plan_b ? hipMemcpyAsync(p_jobs, h, plan_b, hipMemcpyHostToDevice, st) : hipSuccess;
     if (e != hipSuccess) return MPG_E_DEVICE;
     return MPG_OK;
 }
@@ -1177,9 +1166,8 @@ int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg,
     const size_t ngroups = P.groups.size();
     int rc;
     const DpSink sink{X.d_out, X.d_ops, cfg.serve ? 1 : 0, cfg.serve ? 1 : 0};
-    if (launch_status(st, X.d_jobs, X.cnt, sink) != hipSuccess) return MPG_E_DEVICE;
     const int neg_init = -(1 << 30);
-    if (launch_init(st, X.d_jobs, X.cnt, X.d_pst, X.d_prog, X.d_qhead, 16, neg_init) !=
+    if (launch_init(st, X.d_jobs, X.cnt, X.d_pst, X.d_prog, X.d_qhead, 16, neg_init, sink) !=
         hipSuccess)
         return MPG_E_DEVICE;
     if (tm) tm->begin(st, 0);
