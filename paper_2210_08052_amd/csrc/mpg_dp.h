@@ -611,56 +611,68 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
             int nsc[K];
             if (t + 1 < 64) ld_prof(nd0, nsc);
             const int4 ds0 = cd0;
-            const int hl0 = cin.x, il0 = cin.y;
+            int hl0 = cin.x, il0 = cin.y;
             const int z = ds0.y;
             int Hn[K], In[K], Dn[K], An[K], Bn[K], Cn[K];
+            // First every term that does not need the left lane's values of this row,
+            // for all columns, then I and H: the hand-off's latency lies under the first
+            // part (left to itself the compiler waits for it after a few
+            // instructions).
+            int xw[K], xy[K];  // maxima of H's candidates but I
 #pragma unroll
             for (int c = 0; c < K; ++c) {
-                const int L0 = c ? Hn[c - 1] : hl0;
-                const int IL = c ? In[c - 1] : il0;
                 const int L1 = c ? h1[c - 1] : hl1;
                 const int L3 = c ? h3[c - 1] : hl3;
+                const int zc = z;
                 if (!TB) {
                     const int D = vsub<F32>(imax(vsub<F32>(h3[c], cq), d3[c]), ce);
-                    const int I = vsub<F32>(imax(vsub<F32>(L0, cq), IL), ce);
                     const int M = L3 + csc[c];
+                    // frameshifts: F1 and G1 of this row cost f each, and F2, G2 are the
+                    // previous row's F1, G1 (H two rows up is the history one row up), so
+                    // one max per cell covers all four
                     int pf = 0;
                     if (!NOF) {
                         pf = vsub<F32>(imax(L1, h1[c]), cf);
+                        // opaque to the next row: the compiler would otherwise expand
+                        // fp - ... back into four candidates there
                         asm("" : "+v"(pf));
                     }
-                    int H;
                     if (!NOI) {
                         const int A = imax(vsub<F32>(h1[c], ddm1), a1[c]);
                         const int B = imax(vsub<F32>(L1, dd0), b1[c]);
                         const int C = imax(vsub<F32>(L1, ds0.z), c1[c]);
                         An[c] = A; Bn[c] = B; Cn[c] = C;
                         const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
-                        if (!NOF) H = imax3(x, imax3(vsub<F32>(C, aam1), pf, fp[c]), imax3(M, I, z));
-                        else H = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
+                        xw[c] = imax3(M, zc, x);
+                        const int y = vsub<F32>(C, aam1);
+                        xy[c] = NOF ? y : imax3(y, pf, fp[c]);
                     } else {
-                        if (!NOF) H = imax(imax3(D, pf, fp[c]), imax3(M, I, z));
-                        else H = imax(imax3(D, M, I), z);
+                        xw[c] = NOF ? D : imax3(D, pf, fp[c]);
+                        xy[c] = imax(M, zc);
                     }
                     if (!NOF) fp[c] = pf;
-                    Hn[c] = H; In[c] = I; Dn[c] = D;
+                    Dn[c] = D;
                 } else {
                     const int oD = vsub<F32>(h3[c], cqD), xD = vsub<F32>(d3[c], ce);
                     xacc[1][c] = push_open(xacc[1][c], vsub<F32>(xD, oD));
                     int D = imax(oD, xD);
-                    const int oI = vsub<F32>(L0, cq), xI = vsub<F32>(IL, ce);
-                    xacc[0][c] = push_open(xacc[0][c], vsub<F32>(xI, oI));
-                    int I = imax(oI, xI);
                     const int M = L3 + csc[c];
+                    // F1 (nibble 11) and G1 (9) of this row; F2 (10) and G2 (8) are the
+                    // previous row's F1 and G1 less one, so their maximum is the previous
+                    // row's maximum less one
                     int p1 = 0, p2 = 0;
                     if (!NOF) {
                         p1 = imax(vsub<F32>(L1, cf11), vsub<F32>(h1[c], cf9));
+                        // opaque to the next row: the compiler would otherwise expand
+                        // fp - 1 back into four candidates there
                         asm("" : "+v"(p1));
                         p2 = vsub<F32>(fp[c], kOne);
                         fp[c] = p1;
                     }
-                    asm("" : "+v"(D), "+v"(I));
-                    int Hk;
+                    // the states enter H's maximum as they are: left visible, the
+                    // compiler may also build H from their two halves in a second tree
+                    // (seen at one column per lane)
+                    asm("" : "+v"(D));
                     if (!NOI) {
                         const int oA = DDN ? vadd<F32>(h1[c], ddm1) : add3k<2>(h1[c], ddm1);
                         xacc[2][c] = push_open(xacc[2][c], vsub<F32>(a1[c], oA));
@@ -674,17 +686,45 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
                         asm("" : "+v"(A), "+v"(B), "+v"(C));
                         An[c] = A; Bn[c] = B; Cn[c] = C;
                         const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
-                        if (!NOF) Hk = imax3(x, imax3(vsub<F32>(C, aam1), p1, p2), imax3(M, I, z));
-                        else Hk = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
+                        xw[c] = imax3(M, zc, x);
+                        const int y = vsub<F32>(C, aam1);
+                        xy[c] = NOF ? y : imax3(y, p1, p2);
                     } else {
-                        if (!NOF) Hk = imax(imax3(D, p1, p2), imax3(M, I, z));
-                        else Hk = imax(imax3(D, M, I), z);
+                        xw[c] = NOF ? D : imax3(D, p1, p2);
+                        xy[c] = imax(M, zc);
                     }
-                    nacc[c] = __builtin_amdgcn_alignbit(Hk, nacc[c], 4);
-                    Hn[c] = Hk & ~15;
-                    In[c] = I; Dn[c] = D;
+                    Dn[c] = D;
                 }
             }
+#pragma unroll
+            for (int c = 0; c < K; ++c) asm("" : "+v"(hl0), "+v"(il0) : "v"(xw[c]), "v"(xy[c]));
+#pragma unroll
+            for (int c = 0; c < K; ++c) {
+                const int L0 = c ? Hn[c - 1] : hl0;
+                const int IL = c ? In[c - 1] : il0;
+                const int oI = vsub<F32>(L0, cq);
+                if (!TB) {
+                    const int I = vsub<F32>(imax(oI, IL), ce);
+                    Hn[c] = imax3(xw[c], xy[c], I);
+                    In[c] = I;
+                } else {
+                    const int xI = vsub<F32>(IL, ce);
+                    xacc[0][c] = push_open(xacc[0][c], vsub<F32>(xI, oI));
+                    int I = imax(oI, xI);
+                    asm("" : "+v"(I));
+                    const int Hk = imax3(xw[c], xy[c], I);
+                    nacc[c] = __builtin_amdgcn_alignbit(Hk, nacc[c], 4);
+                    Hn[c] = Hk & ~15;
+                    In[c] = I;
+                }
+            }
+            Hout = Hn[K - 1];
+            Iout = In[K - 1];
+            // (the hand-off as in the whole-wave strips)
+            __builtin_amdgcn_sched_barrier(0);
+            out_l[t] = make_int2(Hout, Iout);
+            if (t + 1 < 64) cin = in_l[t + 1];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int c = 0; c < K; ++c)
                 key_push<TB, F32>(bk[c], kp[c], Hn[c], t);
@@ -713,13 +753,9 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
             ddm1 = DDN ? vadd<F32>(dd0, kOne) : dd0;
             dd0 = DDN ? vadd<F32>(ds0.z, kOne) : ds0.z;
             aam2 = aam1; aam1 = ds0.w;
-            Hout = Hn[K - 1];
-            Iout = In[K - 1];
             cd0 = nd0; nd0 = fd0;
 #pragma unroll
             for (int c = 0; c < K; ++c) csc[c] = nsc[c];
-            out_l[t] = make_int2(Hout, Iout);
-            if (t + 1 < 64) cin = in_l[t + 1];
             if (StepBarrier<TB, F32>::value) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
@@ -829,6 +865,9 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
     // 1.05 ms, 1,000 profiles 2.55 -> 2.41; one column with traceback gains 2%
     // alone and loses 7% on 1,500 pairs).
     constexpr bool XLDS = !NOI && (K > 1 || TB);
+    // whether the hand-off is pinned to its place in the step (see below);
+    // the mixed variant is 4% slower with it
+    constexpr bool EARLY = XLDS && !MIXED;
     int out_off = LY::RING + LY::PROF + LY::IN + (lane == 63 ? 0 : 64 + lane) * 8;
     int in_off = lane ? LY::RING + LY::PROF + LY::IN + (62 + lane) * 8 : LY::RING + LY::PROF;
     asm volatile("" : "+v"(in_off), "+v"(out_off));
@@ -1064,76 +1103,71 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                     int2 nin = make_int2(0, 0);
                     if (!XLDS && t + 1 < 64) nin = inb[t + 1];
                     const int4 ds0 = cd0;
-                    const int hl0 = XLDS ? cin.x : shr1(cin.x, Hout);
-                    const int il0 = XLDS ? cin.y : shr1(cin.y, Iout);
+                    int hl0 = XLDS ? cin.x : shr1(cin.x, Hout);
+                    int il0 = XLDS ? cin.y : shr1(cin.y, Iout);
                     const int zr = ds0.y;
                     int Hn[K], In[K], Dn[K], An[K], Bn[K], Cn[K];
-#pragma unroll
-                    for (int c = 0; c < K; ++c) {
-                        const int L0 = c ? Hn[c - 1] : hl0;
-                        const int IL = c ? In[c - 1] : il0;
+                    // First every term that does not need the left lane's values of this row,
+                    // for all columns, then I and H: the hand-off's latency lies under the first
+                    // part (left to itself the compiler waits for it after a few instructions:
+                    // 10k batch 10.2 -> 9.98 ms, one traced pair 0.376 -> 0.370).
+                    // (Kernels that do not pin the hand-off do one column after the other.)
+                    int xw[K], xy[K], xm[K];  // maxima of H's candidates but I; M
+                    auto terms = [&](int c) {
                         const int L1 = c ? h1[c - 1] : hl1;
-                        const int L2 = c ? h2[c - 1] : hl2;
                         const int L3 = c ? h3[c - 1] : hl3;
-                        const int z = floor_mode(SM) ? zr : imin(zr, zl[c]);
+                        const int zc = (floor_mode(SM) ? zr : imin(zr, zl[c]));
                         if (!TB) {
                             const int D = vsub<F32>(imax(vsub<F32>(h3[c], cqDv[c]), d3[c]), ceDv[c]);
-                            // column 0 takes I(i, j-1) from the left lane inside
-                            // the max (lane 0 from the boundary row)
-                            const int oI = vsub<F32>(L0, cqv[c]);
-                            const int I = vsub<F32>(imax(oI, IL), cev[c]);
                             const int M = L3 + csc[c];
-                            // frameshifts: F1 and G1 of this row cost f each, and F2,
-                            // G2 are the previous row's F1, G1 (H two rows up is the
-                            // history one row up), so one max per cell covers all four
+                            xm[c] = M;
+                            // frameshifts: F1 and G1 of this row cost f each, and F2, G2 are the
+                            // previous row's F1, G1 (H two rows up is the history one row up), so
+                            // one max per cell covers all four
                             int pf = 0;
                             if (!NOF) {
                                 pf = vsub<F32>(imax(L1, h1[c]), cf);
-                                // opaque to the next row: the compiler would otherwise
-                                // expand fp - ... back into four candidates there
+                                // opaque to the next row: the compiler would otherwise expand
+                                // fp - ... back into four candidates there
                                 asm("" : "+v"(pf));
                             }
-                            int H;
                             if (!NOI) {
                                 const int A = imax(vsub<F32>(h1[c], ddm1), a1[c]);
                                 const int B = imax(vsub<F32>(L1, dd0), b1[c]);
                                 const int C = imax(vsub<F32>(L1, ds0.z), c1[c]);
                                 An[c] = A; Bn[c] = B; Cn[c] = C;
                                 const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
-                                if (!NOF) H = imax3(x, imax3(vsub<F32>(C, aam1), pf, fp[c]), imax3(M, I, z));
-                                else H = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
+                                xw[c] = EARLY ? imax3(M, zc, x) : x;
+                                const int y = vsub<F32>(C, aam1);
+                                xy[c] = NOF ? y : imax3(y, pf, fp[c]);
                             } else {
-                                if (!NOF) H = imax(imax3(D, pf, fp[c]), imax3(M, I, z));
-                                else H = imax(imax3(D, M, I), z);
+                                xw[c] = NOF ? D : imax3(D, pf, fp[c]);
+                                xy[c] = EARLY ? imax(M, zc) : xw[c];
                             }
                             if (!NOF) fp[c] = pf;
-                            Hn[c] = H; In[c] = I; Dn[c] = D;
+                            Dn[c] = D;
                         } else {
                             const int oD = vsub<F32>(h3[c], cqDv[c]), xD = vsub<F32>(d3[c], ceDv[c]);
                             xacc[1][c] = push_open(xacc[1][c], vsub<F32>(xD, oD));
                             int D = imax(oD, xD);
-                            const int oI = vsub<F32>(L0, cqv[c]);
-                            const int xI = vsub<F32>(IL, cev[c]);
-                            xacc[0][c] = push_open(xacc[0][c], vsub<F32>(xI, oI));
-                            int I = imax(oI, xI);
                             const int M = L3 + csc[c];
-                            // F1 (nibble 11) and G1 (9) of this row; F2 (10) and G2
-                            // (8) are the previous row's F1 and G1 less one, so their
-                            // maximum is the previous row's maximum less one
+                            xm[c] = M;
+                            // F1 (nibble 11) and G1 (9) of this row; F2 (10) and G2 (8) are the
+                            // previous row's F1 and G1 less one, so their maximum is the previous
+                            // row's maximum less one
                             int p1 = 0, p2 = 0;
                             if (!NOF) {
                                 p1 = imax(vsub<F32>(L1, cf11), vsub<F32>(h1[c], cf9));
-                                // opaque to the next row: the compiler would otherwise
-                                // expand fp - 1 back into four candidates there
+                                // opaque to the next row: the compiler would otherwise expand
+                                // fp - 1 back into four candidates there
                                 asm("" : "+v"(p1));
                                 p2 = vsub<F32>(fp[c], kOne);
                                 fp[c] = p1;
                             }
-                            // the states enter H's maximum as they are: left visible,
-                            // the compiler may also build H from their two halves in a
-                            // second tree (seen at one column per lane)
-                            asm("" : "+v"(D), "+v"(I));
-                            int Hk;
+                            // the states enter H's maximum as they are: left visible, the
+                            // compiler may also build H from their two halves in a second tree
+                            // (seen at one column per lane)
+                            asm("" : "+v"(D));
                             if (!NOI) {
                                 const int oA = DDN ? vadd<F32>(h1[c], ddm1) : add3k<2>(h1[c], ddm1);
                                 xacc[2][c] = push_open(xacc[2][c], vsub<F32>(a1[c], oA));
@@ -1147,16 +1181,61 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                                 asm("" : "+v"(A), "+v"(B), "+v"(C));
                                 An[c] = A; Bn[c] = B; Cn[c] = C;
                                 const int x = imax3(D, vsub<F32>(A, ds0.w), vsub<F32>(B, aam2));
-                                if (!NOF) Hk = imax3(x, imax3(vsub<F32>(C, aam1), p1, p2), imax3(M, I, z));
-                                else Hk = imax3(x, imax3(vsub<F32>(C, aam1), M, I), z);
+                                xw[c] = EARLY ? imax3(M, zc, x) : x;
+                                const int y = vsub<F32>(C, aam1);
+                                xy[c] = NOF ? y : imax3(y, p1, p2);
                             } else {
-                                if (!NOF) Hk = imax(imax3(D, p1, p2), imax3(M, I, z));
-                                else Hk = imax(imax3(D, M, I), z);
+                                xw[c] = NOF ? D : imax3(D, p1, p2);
+                                xy[c] = EARLY ? imax(M, zc) : xw[c];
                             }
+                            Dn[c] = D;
+                        }
+                    };
+                    auto best_of = [&](int c, int I) {
+                        if (EARLY) return imax3(xw[c], xy[c], I);
+                        const int z = floor_mode(SM) ? zr : imin(zr, zl[c]);
+                        if (NOI) return imax(xw[c], imax3(xm[c], I, z));
+                        return imax3(xw[c], xy[c], imax3(xm[c], I, z));
+                    };
+                    auto finish = [&](int c) {
+                        const int L0 = c ? Hn[c - 1] : hl0;
+                        const int IL = c ? In[c - 1] : il0;
+                        const int oI = vsub<F32>(L0, cqv[c]);
+                        if (!TB) {
+                            const int I = vsub<F32>(imax(oI, IL), cev[c]);
+                            Hn[c] = best_of(c, I);
+                            In[c] = I;
+                        } else {
+                            const int xI = vsub<F32>(IL, cev[c]);
+                            xacc[0][c] = push_open(xacc[0][c], vsub<F32>(xI, oI));
+                            int I = imax(oI, xI);
+                            asm("" : "+v"(I));
+                            const int Hk = best_of(c, I);
                             nacc[c] = __builtin_amdgcn_alignbit(Hk, nacc[c], 4);
                             Hn[c] = Hk & ~15;
-                            In[c] = I; Dn[c] = D;
+                            In[c] = I;
                         }
+                    };
+#pragma unroll
+                    for (int c = 0; c < K; ++c) {
+                        terms(c);
+                        if (!EARLY) finish(c);
+                    }
+                    if (EARLY) {
+#pragma unroll
+                        for (int c = 0; c < K; ++c) asm("" : "+v"(hl0), "+v"(il0) : "v"(xw[c]), "v"(xy[c]));
+#pragma unroll
+                        for (int c = 0; c < K; ++c) finish(c);
+                    }
+                    Hout = Hn[K - 1];
+                    Iout = In[K - 1];
+                    if (EARLY) {
+                        // the hand-off at once, and in this order: what follows
+                        // it here and the next step's first part cover its latency
+                        __builtin_amdgcn_sched_barrier(0);
+                        out_l[t] = make_int2(Hout, Iout);
+                        if (t + 1 < 64) cin = in_l[t + 1];
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                     // end-cell tracking (chunk-local, merged after the chunk)
                     if constexpr (MIXED) {
@@ -1226,11 +1305,11 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                     ddm1 = DDN ? vadd<F32>(dd0, kOne) : dd0;
                     dd0 = DDN ? vadd<F32>(ds0.z, kOne) : ds0.z;
                     aam2 = aam1; aam1 = ds0.w;
-                    Hout = Hn[K - 1];
-                    Iout = In[K - 1];
-                    out_l[t] = make_int2(Hout, Iout);
-                    if (!XLDS) cin = nin;
-                    else if (t + 1 < 64) cin = in_l[t + 1];
+                    if (!EARLY) {
+                        out_l[t] = make_int2(Hout, Iout);
+                        if (!XLDS) cin = nin;
+                        else if (t + 1 < 64) cin = in_l[t + 1];
+                    }
                     // rotate the pipeline
                     cd0 = nd0; nd0 = fd0;
 #pragma unroll
