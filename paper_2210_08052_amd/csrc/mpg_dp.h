@@ -20,15 +20,6 @@
 #ifndef MPG_TB_WAVES
 #define MPG_TB_WAVES 3
 #endif
-// A scheduling barrier between the steps of a chunk keeps each step's
-// instructions together (bounding the registers the unrolled chunk needs):
-// kept in the integer score-only kernels, left out of the traceback ones (2%
-// faster with neighbouring steps interleaved, 10k batch) and of the fp32 ones
-// (10k batch 10.43 -> 10.32 ms, rescoring 3,000 pairs 1.62 -> 1.59 ms).
-template <bool TB, bool F32>
-struct StepBarrier {
-    static constexpr bool value = !TB && !F32;
-};
 #ifndef MPG_TB1_WAVES
 #define MPG_TB1_WAVES 4
 #endif
@@ -237,18 +228,30 @@ __device__ __forceinline__ int vnum(int v) {
 // take (exponents of 2^21 to 2^24).
 // The keys of two consecutive steps enter one three-input max: an even step
 // leaves its key in kp, the odd one takes both (64 steps: none is left over).
-template <bool TB, bool F32>
+// Each is kept in its step: left free, the compiler takes the maxima of a
+// chunk's 64 keys at its end and spills every step's H until then (widths 1
+// and 2 hold 128 or 168 VGPRs; integer form at width 2, 10,000 pairs: 19.8 ms
+// with 127 spilled, 15.2 so).  The integer form of width 4 runs one wavefront
+// per SIMD with registers to spare, where free maxima cover latency (3,000
+// pairs 5.9 ms, kept 7.9).
+template <int K, bool F32>
+struct PinKeys {
+    static constexpr bool value = F32 || K <= 2;
+};
+template <int K, bool TB, bool F32>
 __device__ __forceinline__ void key_push(int& bk, int& kp, int h, int t) {
     const int k = (int)(((uint32_t)h << (TB ? 2 : 6)) | (uint32_t)(63 - t));
-    if (!F32) {
-        bk = k > bk ? k : bk;
+    if (!PinKeys<K, F32>::value) {
+        bk = imax(k, bk);
         return;
     }
     if (t & 1) {
-        const uint32_t q = (uint32_t)kp > (uint32_t)k ? (uint32_t)kp : (uint32_t)k;
-        bk = (int)(q > (uint32_t)bk ? q : (uint32_t)bk);
-        // kept in this step: left free, the compiler takes the maxima of a
-        // chunk's 64 keys at its end and spills every step's H until then
+        if (F32) {
+            const uint32_t q = (uint32_t)kp > (uint32_t)k ? (uint32_t)kp : (uint32_t)k;
+            bk = (int)(q > (uint32_t)bk ? q : (uint32_t)bk);
+        } else {
+            bk = imax3(kp, k, bk);
+        }
         asm volatile("" : "+v"(bk));
     } else {
         kp = k;
@@ -727,7 +730,7 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int c = 0; c < K; ++c)
-                key_push<TB, F32>(bk[c], kp[c], Hn[c], t);
+                key_push<K, TB, F32>(bk[c], kp[c], Hn[c], t);
             if (TB && (t & 7) == 7) {
 #pragma unroll
                 for (int c = 0; c < K; ++c)
@@ -756,7 +759,6 @@ __device__ __forceinline__ void seg_item(const int2 item, const PairJob* __restr
             cd0 = nd0; nd0 = fd0;
 #pragma unroll
             for (int c = 0; c < K; ++c) csc[c] = nsc[c];
-            if (StepBarrier<TB, F32>::value) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int c = 0; c < K; ++c) {
@@ -1246,12 +1248,14 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                         for (int c = 0; c < K; ++c) {
                             const int v = take ? Hn[c] : NEG;
                             if (F32) {  // one key, as in LOCAL
-                                key_push<TB, F32>(bk[c], kp[c], v, t);
+                                key_push<K, TB, F32>(bk[c], kp[c], v, t);
                                 continue;
                             }
                             const bool gt = v > bk[c];
                             bk[c] = gt ? v : bk[c];
                             bkt[c] = gt ? t : bkt[c];
+                            if (PinKeys<K, F32>::value)
+                                asm volatile("" : "+v"(bk[c]), "+v"(bkt[c]));
                         }
                     } else if (fixed_end_mode(MODE)) {
                         const bool at_n = (lane == t + srow_n);
@@ -1267,13 +1271,15 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                     } else if (MODE == MPG_LOCAL || F32) {
 #pragma unroll
                         for (int c = 0; c < K; ++c)
-                            key_push<TB, F32>(bk[c], kp[c], Hn[c], t);
+                            key_push<K, TB, F32>(bk[c], kp[c], Hn[c], t);
                     } else {
 #pragma unroll
                         for (int c = 0; c < K; ++c) {
                             const bool gt = Hn[c] > bk[c];
                             bk[c] = gt ? Hn[c] : bk[c];
                             bkt[c] = gt ? t : bkt[c];
+                            if (PinKeys<K, F32>::value)
+                                asm volatile("" : "+v"(bk[c]), "+v"(bkt[c]));
                         }
                     }
                     if (TB && (t & 7) == 7) {
@@ -1314,7 +1320,6 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                     cd0 = nd0; nd0 = fd0;
 #pragma unroll
                     for (int c = 0; c < K; ++c) csc[c] = nsc[c];
-                    if (StepBarrier<TB, F32>::value) __builtin_amdgcn_sched_barrier(0);
                 }  // steps
 
                 // merge the chunk's best into the strip's best (first maximum)
