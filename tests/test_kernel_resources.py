@@ -74,3 +74,11 @@ def test_integer_form_without_spills(kernels, K):
     fp32 form>: the integer form at widths 1 and 2."""
     for args, k in _select(kernels, "dp_kernel", (K, None, None, None, None, None, 0)).items():
         assert k[".vgpr_spill_count"] == 0, (args, k[".vgpr_count"], k[".vgpr_spill_count"])
+
+
+@pytest.mark.parametrize("K", [1, 2])
+def test_int16_without_spills(kernels, K):
+    """<columns per lane, no introns, no frameshifts, three-input form>: both
+    forms of the 16-bit kernel."""
+    for args, k in _select(kernels, "dp16_kernel", (K, None, None, None)).items():
+        assert k[".vgpr_spill_count"] == 0, (args, k[".vgpr_count"], k[".vgpr_spill_count"])
