@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "mpg_internal.h"
+#include "mpg_width.h"
 
 using namespace mpg;
 
@@ -352,7 +353,7 @@ struct Tuning {
 // Columns per lane: one width for the pairs of a call wider than 64 columns
 // (pairs of one width share a launch; mixed widths would split the device
 // between concurrent persistent launches): a forced width, else the tuned
-// one, else 0: the call's own work decides (width_by_work).  Pairs of at most
+// one, else 0: the call's own work decides (WidthWork).  Pairs of at most
 // 64 columns take width 1.
 int choose_width(const Overrides& ov, const Tuning* tu, int force) {
     if (ov.K == 1 || ov.K == 2 || ov.K == 4) return ov.K;
@@ -371,15 +372,6 @@ int choose_K16(const Overrides& ov, const Tuning* tu, int force = 0) {
 
 int g_num_cu = 256;  // compute units of the device (the DP grid is sized per CU)
 
-// Steps every strip of a pair runs (a multiple of 64).  Lane L reaches row
-// n at step n + L: a pair of one strip stops once the lane of column m has,
-// the strips of a wider pair run all 64 lanes to row n.
-int pair_nsteps(int n, int m, int K) {
-    const int nstrips = (m + 1 + 64 * K - 1) / (64 * K);
-    const int lanes = nstrips == 1 ? m / K + 1 : 64;
-    return ((n + lanes + 63) / 64) * 64;
-}
-
 int64_t tb_bytes_of(int n, int m, int K) {
     const int nsteps = pair_nsteps(n, m, K);
     const int nstrips = (m + 1 + 64 * K - 1) / (64 * K);
@@ -390,45 +382,6 @@ int64_t tb_bytes_of(int n, int m, int K) {
 int64_t tb_bytes_max(int n, int m) {
     return std::max({tb_bytes_of(n, m, 1), tb_bytes_of(n, m, 2), tb_bytes_of(n, m, 4)});
 }
-
-// Width 1 or 2 for a call, from what bounds it.  A call takes at least its
-// work (strips x steps) spread over the device's SIMDs, and at least the
-// longest pair's own chain: its steps one after another, each strip 128 steps
-// behind the one on its left.  Width 2 does a column's work in fewer
-// instructions, width 1 makes a step shorter.  Cycles of one step, measured on
-// the 10k batch's pairs: on a SIMD shared by four wavefronts 149 and 93
-// (score-only), 250 and 133 (traceback); alone, 245 and 165, 390 and 250: a
-// part per step and a part per column, of which the intron states are half.
-// (Without introns a step alone mostly waits for the hand-off between lanes:
-// rescoring 100 pairs takes 0.95 ms at width 1, 0.91 at width 2.)
-// Times at widths 2 and 1: one traced pair 0.56 and 0.39 ms, 800 traced pairs
-// 4.74 and 3.41, 3,000 6.35 and 6.45, 6,000 11.2 and 11.9; score-only 1,500
-// pairs 3.5 and 2.45, 3,000 3.67 and 4.04, 10,000 10.2 and 12.5 ms.
-struct WidthWork {
-    double work[2] = {0, 0}, chain[2] = {0, 0};  // [0]: width 1, [1]: width 2
-    struct Cost { double step, column; };
-    void add(int n, int m, const Cost& sh, const Cost& al) {
-        for (int K = 1; K <= 2; ++K) {
-            const double steps = pair_nsteps(n, m, K);
-            const double strips = (m + 64 * K) / (64 * K);
-            work[K - 1] += (sh.step + sh.column * K) * steps * strips;
-            chain[K - 1] = std::max(chain[K - 1],
-                                    (al.step + al.column * K) * (steps + 128 * (strips - 1)));
-        }
-    }
-    // int16 lanes: a step advances two pairs
-    void add16(int n, int m) { add(n, m, Cost{14, 54}, Cost{90, 120}); }
-    void add(int n, int m, bool tb, bool introns) {
-        static constexpr Cost kShared[2][2] = {{{37, 28}, {37, 56}}, {{16, 58}, {16, 117}}};
-        static constexpr Cost kAlone[2][2] = {{{140, 20}, {85, 80}}, {{150, 60}, {110, 140}}};
-        add(n, m, kShared[tb][introns], kAlone[tb][introns]);
-    }
-    int width(int ncu) const {
-        const double t1 = std::max(work[0] / (4 * ncu), chain[0]);
-        const double t2 = std::max(work[1] / (4 * ncu), chain[1]);
-        return t1 < t2 ? 1 : 2;
-    }
-};
 
 // Bound on |value| of reachable cells (see the public header): the largest
 // match score times the protein length, and (EXTEND/GLOBAL, whose H has no 0
