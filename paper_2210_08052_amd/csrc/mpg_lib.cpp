@@ -555,6 +555,10 @@ void sort_by_key(std::vector<std::pair<int64_t, int32_t>>& v, bool descending,
     }
 }
 
+bool seg_tb(const mpg_seg& s, const mpg_params* p) {
+    return ((s.flags | p->flags) & MPG_WANT_TB) != 0;
+}
+
 // Build the plan for the pairs idx[0..cnt) of a call with n pairs.  Each
 // job writes result record idx[k] and its op string at ops_off[idx[k]].
 void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, int32_t cnt,
@@ -580,14 +584,24 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     int K16 = choose_K16(ov, cfg.tune, cfg.force_K16);
     int width = choose_width(ov, cfg.tune, cfg.force_K);
     const bool by_work = width == 0 && !cfg.wide;
+    auto pair_bound = [&](int32_t q) {
+        return cfg.pro ? bound.profile(cfg.pro_bounds[2 * q], cfg.pro_bounds[2 * q + 1]) : bound;
+    };
+    auto pair_mode = [&](int32_t q) { return cfg.modes ? (int)cfg.modes[q] : (int)p->mode; };
+    // lengths and scores within the limits (else the pair's record says MPG_E_RANGE)
+    auto in_range = [&](int32_t q, const BoundInfo& b) {
+        const mpg_seg& s = segs[q];
+        return s.dlen >= 0 && s.plen >= 0 && s.dlen <= MPG_MAX_DNA && s.plen <= MPG_MAX_PROT &&
+               b.ok(s.dlen, s.plen, pair_mode(q));
+    };
     if (by_work) {
         WidthWork ww, ww16;
         for (int32_t k = 0; k < cnt; ++k) {
             const mpg_seg& s = segs[idx[k]];
-            const int nn = std::max(0, s.dlen), mm = std::max(0, s.plen);
-            const bool tb = ((s.flags | p->flags) & MPG_WANT_TB) != 0;
-            if (allow16 && !tb && bound.ok16(mm, p->mode)) ww16.add16(nn, mm);
-            else ww.add(nn, mm, tb, bound.introns);
+            if (!in_range(idx[k], pair_bound(idx[k]))) continue;  // will not run
+            const bool tb = seg_tb(s, p);
+            if (allow16 && !tb && bound.ok16(s.plen, p->mode)) ww16.add16(s.dlen, s.plen);
+            else ww.add(s.dlen, s.plen, tb, bound.introns);
         }
         width = ww.width(cfg.ncu);
         if (K16 == 0) K16 = ww16.width(cfg.ncu);
@@ -636,13 +650,9 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.dna_off = s.dna_off;
         J.prot_off = s.prot_off;
         J.status = MPG_OK;
-        J.mode = cfg.modes ? cfg.modes[idx[k]] : p->mode;
-        const BoundInfo bk = cfg.pro ? bound.profile(cfg.pro_bounds[2 * idx[k]],
-                                                     cfg.pro_bounds[2 * idx[k] + 1])
-                                     : bound;
-        if (s.dlen < 0 || s.plen < 0 || s.dlen > MPG_MAX_DNA || s.plen > MPG_MAX_PROT ||
-            !bk.ok(s.dlen, s.plen, J.mode))
-            J.status = MPG_E_RANGE;
+        J.mode = pair_mode(idx[k]);
+        const BoundInfo bk = pair_bound(idx[k]);
+        if (!in_range(idx[k], bk)) J.status = MPG_E_RANGE;
         const bool want_tb = ((s.flags | p->flags) & MPG_WANT_TB) != 0;
         const int nn = std::max(0, J.n), mm = std::max(0, J.m);
         // a pair whose columns fit one strip of 64 takes one column per lane:
@@ -1196,10 +1206,6 @@ int run_dev(hipStream_t st, Workspace& ws, const mpg_params* p, const uint8_t* d
     int rc = prepare(st, ws, p, d_prot, d_dna, segs, idx, cnt, ops_off, d_out, d_ops, cfg, X);
     if (rc != MPG_OK) return rc;
     return enqueue(st, ws, X, cfg, true);
-}
-
-bool seg_tb(const mpg_seg& s, const mpg_params* p) {
-    return ((s.flags | p->flags) & MPG_WANT_TB) != 0;
 }
 
 // Run all n pairs.  Traceback pairs whose direction bits together exceed the
