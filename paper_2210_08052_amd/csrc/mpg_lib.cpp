@@ -646,30 +646,30 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.n = s.dlen;
         J.m = s.plen;
         J.res = idx[k];
-        J.tb = ((s.flags | p->flags) & MPG_WANT_TB) ? 1 : 0;
+        J.tb = seg_tb(s, p) ? 1 : 0;
         J.dna_off = s.dna_off;
         J.prot_off = s.prot_off;
         J.status = MPG_OK;
         J.mode = pair_mode(idx[k]);
         const BoundInfo bk = pair_bound(idx[k]);
         if (!in_range(idx[k], bk)) J.status = MPG_E_RANGE;
-        const bool want_tb = ((s.flags | p->flags) & MPG_WANT_TB) != 0;
         const int nn = std::max(0, J.n), mm = std::max(0, J.m);
         // a pair whose columns fit one strip of 64 takes one column per lane:
         // wider lanes would only add idle columns to every step
         int K = (mm + 1 <= narrow && !ov.K && !cfg.force_K) ? 1 : width;
-        // (at the traceback budget's edge, the width that needs less)
-        if (by_work && K == 1 && mm + 1 > narrow && want_tb &&
-            (uint64_t)tb_bytes_of(nn, mm, 1) > tb_budget)
-            K = 2;
         if (cfg.pro && K > 2) K = 2;  // profile kernels come in widths 1 and 2
+        // Where the call's work chose the width, a pair is refused for its
+        // direction bits by what they need at width 2, whatever else is in the
+        // call; one that needs more than the budget at width 1 takes width 2.
+        const int K_need = by_work && mm + 1 > narrow ? 2 : K;
+        if (J.tb && J.status == MPG_OK && (uint64_t)tb_bytes_of(nn, mm, K_need) > tb_budget)
+            J.status = MPG_E_RANGE;
+        if (K < K_need && J.tb && (uint64_t)tb_bytes_of(nn, mm, K) > tb_budget) K = K_need;
         J.K = K;
         const int nsteps = pair_nsteps(nn, mm, K);
         J.nchunks = nsteps / 64;
         J.nstrips = (mm + 1 + 64 * K - 1) / (64 * K);
         J.f32 = !ov.no_f32 && bk.f32_ok(nn, mm, J.mode, J.tb != 0) ? 1 : 0;
-        if (J.tb && J.status == MPG_OK && (uint64_t)tb_bytes_of(nn, mm, K) > tb_budget)
-            J.status = MPG_E_RANGE;
         J.ops_off = ops_off[idx[k]];
         J.i16 = 0;
         if (J.status != MPG_OK) continue;

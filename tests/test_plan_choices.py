@@ -1,5 +1,6 @@
 """What a call's plan may depend on: pairs that only get an error record do not
-move the others' strip width."""
+move the others' strip width, and a pair is refused for its direction bits
+whatever else is in the call."""
 import numpy as np
 import pytest
 
@@ -47,3 +48,21 @@ def test_refused_pairs_do_not_choose_the_width(beyond):
     assert packs2 == packs
     assert got["status"][-1] == mpg.MPG_E_RANGE
     assert (got["status"][:-1] == 0).all() and (got["score"][:-1] == ref["score"]).all()
+
+
+@pytest.mark.parametrize("budget,status", [(313343, mpg.MPG_E_RANGE), (313344, 0)])
+def test_budget_refusal_does_not_hang_on_the_call(budget, status):
+    """A traced pair of 150 residues on 1,000 bases: 17 chunks of 4,608 bytes per
+    column, 2 strips of width 2 (313,344 bytes) or 3 of width 1 (235,008).  Its
+    refusal goes by width 2, alone (the call's work would choose width 1) and
+    among 3,000 others (width 2)."""
+    rng = np.random.default_rng(6)
+    prot = bytes(rng.choice(list(b"ARNDCQEGHILKMFPSTWYV"), 300).astype(np.uint8))
+    dna = bytes(rng.choice(list(b"ACGT"), 1000).astype(np.uint8))
+    print("case budget %d" % budget, flush=True)
+    with mpg.Context(0, tb_budget_bytes=budget) as ctx:
+        one = (prot[:150], dna, True)
+        alone = ctx.align_batch([one], mpg.params())
+        among = ctx.align_batch([one] + [(prot, dna, False)] * 3000, mpg.params())
+    assert alone[0]["status"] == status
+    assert among[0] == dict(alone[0], job_id=among[0]["job_id"])
