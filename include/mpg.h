@@ -382,7 +382,9 @@ int64_t mpg_chain_ops_capacity(const mpg_params *p, const mpg_chain_seg *chains,
  * waits only for the previous call's use of each workspace, not for the whole
  * stream.  The second half runs on a stream of the context's, forked from and
  * joined to the context's stream.  Every chain is checked before any work is
- * enqueued. */
+ * enqueued.  Below 2,048 chains the halves share the traceback budget; a call
+ * with a chain whose region could need more than half of it, or whose halves
+ * do not fit the device's memory, runs as one batch. */
 int mpg_align_chains_dev(mpg_ctx *ctx, const mpg_params *p, const uint8_t *d_prot,
                          const uint8_t *d_dna, const mpg_chain_seg *chains, int32_t n,
                          mpg_dev_result *d_out, char *d_ops, int64_t ops_cap);

@@ -2201,10 +2201,23 @@ int mpg_align_chains_dev(mpg_ctx* ctx, const mpg_params* p, const uint8_t* d_pro
     // joined to it at its end: each sub-batch lasts at least as long as its
     // longest piece's chain of steps, so one after the other the call would
     // take twice that (3,000 chains 5.45 -> 3.63 ms; 1,500 in one batch 3.2,
-    // in two 2.85 ms).  Every chain is checked
-    // before either is enqueued, so an invalid call does no work.
-    const int nsub = n >= 512 ? 2 : 1;
-    if (nsub == 1)
+    // in two 2.85 ms).  Every chain is checked before either is enqueued, so an
+    // invalid call does no work.
+    // Below 2,048 chains the halves take no more device memory than one batch:
+    // each gets half of the traceback budget, where no piece can need more
+    // (else the call is one batch), and a call whose halves do not fit the
+    // device runs as one batch after all.
+    constexpr int32_t kHalves = 512, kHalvesAlways = 2048;
+    bool halves = n >= kHalves;
+    if (halves && n < kHalvesAlways) {
+        cfg.tb_budget /= 2;
+        for (int32_t c = 0; c < n && halves; ++c)
+            halves = !chain_tb(chains[c], p) || chains[c].plen < 0 || chains[c].dlen < 0 ||
+                     chains[c].plen > MPG_MAX_PROT || chains[c].dlen > kMaxChainDna ||
+                     (uint64_t)tb_bytes_max(chains[c].dlen, chains[c].plen) <= cfg.tb_budget;
+        if (!halves) cfg.tb_budget = ctx->tb_budget;
+    }
+    if (!halves)
         return chains_dev(ctx->stream, ctx->ws, p, d_prot, d_dna, chains, n, d_out, d_ops,
                           ops_cap, cfg);
     for (int32_t c = 0; c < n; ++c)
@@ -2228,19 +2241,27 @@ int mpg_align_chains_dev(mpg_ctx* ctx, const mpg_params* p, const uint8_t* d_pro
         hipStreamWaitEvent(ctx->chain_side, ctx->chain_fork, 0) != hipSuccess)
         return MPG_E_DEVICE;
     int64_t ops_base = 0;
-    for (int sb = 0; sb < nsub; ++sb) {
-        const int32_t lo = (int32_t)((int64_t)n * sb / nsub);
-        const int32_t hi = (int32_t)((int64_t)n * (sb + 1) / nsub);
-        Workspace& w = ctx->chain_ws[sb & 1];
+    for (int sb = 0; sb < 2; ++sb) {
+        const int32_t lo = sb ? n / 2 : 0, hi = sb ? n : n / 2;
+        Workspace& w = ctx->chain_ws[sb];
         const hipStream_t st = sb ? ctx->chain_side : ctx->stream;
         RunCfg c = cfg;
-        c.ws_ready = ctx->chain_ev[sb & 1];  // never recorded yet: complete
+        c.ws_ready = ctx->chain_ev[sb];  // never recorded yet: complete
         rc = chains_dev(st, w, p, d_prot, d_dna, chains + lo, hi - lo, d_out + lo, d_ops, ops_cap,
                         c, ops_base);
         // (also after an error: the context stream follows what was enqueued)
-        if (hipEventRecord(ctx->chain_ev[sb & 1], st) != hipSuccess ||
-            (sb && hipStreamWaitEvent(ctx->stream, ctx->chain_ev[sb & 1], 0) != hipSuccess))
+        if (hipEventRecord(ctx->chain_ev[sb], st) != hipSuccess ||
+            (sb && hipStreamWaitEvent(ctx->stream, ctx->chain_ev[sb], 0) != hipSuccess))
             return MPG_E_DEVICE;
+        if (rc == MPG_E_NOMEM && n < kHalvesAlways) {
+            if (hipStreamSynchronize(ctx->stream) != hipSuccess ||
+                hipStreamSynchronize(ctx->chain_side) != hipSuccess)
+                return MPG_E_DEVICE;
+            for (auto& q : ctx->chain_ws) q.release();
+            cfg.tb_budget = ctx->tb_budget;
+            return chains_dev(ctx->stream, ctx->ws, p, d_prot, d_dna, chains, n, d_out, d_ops,
+                              ops_cap, cfg);
+        }
         if (rc != MPG_OK) return rc;
         ops_base += mpg_chain_ops_capacity(p, chains + lo, hi - lo);
     }
