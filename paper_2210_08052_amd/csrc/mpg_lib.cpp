@@ -584,8 +584,10 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     int K16 = choose_K16(ov, cfg.tune, cfg.force_K16);
     int width = choose_width(ov, cfg.tune, cfg.force_K);
     const bool by_work = width == 0 && !cfg.wide;
-    auto pair_bound = [&](int32_t q) {
-        return cfg.pro ? bound.profile(cfg.pro_bounds[2 * q], cfg.pro_bounds[2 * q + 1]) : bound;
+    BoundInfo own(bound);  // a profile's
+    auto pair_bound = [&](int32_t q) -> const BoundInfo& {
+        if (!cfg.pro) return bound;
+        return own = bound.profile(cfg.pro_bounds[2 * q], cfg.pro_bounds[2 * q + 1]);
     };
     auto pair_mode = [&](int32_t q) { return cfg.modes ? (int)cfg.modes[q] : (int)p->mode; };
     // lengths and scores within the limits (else the pair's record says MPG_E_RANGE)
@@ -651,7 +653,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.prot_off = s.prot_off;
         J.status = MPG_OK;
         J.mode = pair_mode(idx[k]);
-        const BoundInfo bk = pair_bound(idx[k]);
+        const BoundInfo& bk = pair_bound(idx[k]);
         if (!in_range(idx[k], bk)) J.status = MPG_E_RANGE;
         const int nn = std::max(0, J.n), mm = std::max(0, J.m);
         // a pair whose columns fit one strip of 64 takes one column per lane:
