@@ -564,8 +564,8 @@ int mpg_get_stats(mpg_ctx *ctx, mpg_stats *st);
 
 /* Cumulative device time of the batch calls of this context, measured with
  * hipEvents on the context's stream around the prepass kernel, the DP kernels
- * and the traceback walk (only while timing is enabled).  The halves of a
- * large anchor-driven call overlap, and each counts its own time. */
+ * and the traceback walk (only while timing is enabled).  Where the halves of
+ * a large anchor-driven call overlap, their common time counts once. */
 typedef struct {
     double prepass_ms, dp_ms, walk_ms;
     uint64_t dp_spans; /* number of timed DP spans (one per batch wave) */

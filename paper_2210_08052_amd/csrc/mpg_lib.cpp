@@ -3034,14 +3034,25 @@ int mpg_get_timing(mpg_ctx* ctx, mpg_timing* t, int reset) {
     if (!ctx || !t) return MPG_E_INVAL;
     std::lock_guard<std::mutex> lk(ctx->batch_mu);
     hipSetDevice(ctx->device);
+    // Spans of one kind, in the order they were enqueued; the halves of an
+    // anchor-driven call overlap on the device, and their common time counts
+    // once: a span adds what it lasts beyond the latest end before it.
     auto drain = [&](std::vector<std::pair<hipEvent_t, hipEvent_t>>& v, double& acc,
                      uint64_t* cnt) -> int {
+        hipEvent_t last = nullptr;
         for (auto& pr : v) {
             if (hipEventSynchronize(pr.second) != hipSuccess) return MPG_E_DEVICE;
-            float ms = 0.f;
+            float ms = 0.f, beyond = 0.f;
             if (hipEventElapsedTime(&ms, pr.first, pr.second) != hipSuccess) return MPG_E_DEVICE;
-            acc += ms;
+            if (last && hipEventElapsedTime(&beyond, last, pr.second) != hipSuccess)
+                return MPG_E_DEVICE;
+            if (!last || beyond > 0.f) {
+                acc += last ? std::min(ms, beyond) : ms;
+                last = pr.second;
+            }
             if (cnt) ++*cnt;
+        }
+        for (auto& pr : v) {
             ctx->ev_pool.push_back(pr.first);
             ctx->ev_pool.push_back(pr.second);
         }

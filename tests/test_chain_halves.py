@@ -193,3 +193,27 @@ def test_a_half_without_memory(chains, n, half):
         ctx.sync()
         call.check()
     assert not pool.live
+
+
+@pytest.mark.parametrize("n", [511, 600, 2100])
+def test_timing_counts_overlap_once(chains, n):
+    """The device time of the DP kernels, added over calls that run one at a
+    time, is less than the calls' own time, also where halves overlap."""
+    import time
+    call = _Call(chains, n)
+    with mpg.Context(0) as ctx:
+        call.run(ctx)
+        ctx.sync()
+        ctx.enable_timing(True)
+        ctx.timing(reset=True)
+        t0 = time.perf_counter()
+        for _ in range(10):
+            call.run(ctx)
+            ctx.sync()
+        wall = (time.perf_counter() - t0) * 1e3
+        t = ctx.timing(reset=True)
+    print("case timing n=%d wall %.3f dp %.3f prepass %.3f walk %.3f" %
+          (n, wall, t["dp_ms"], t["prepass_ms"], t["walk_ms"]), flush=True)
+    assert t["dp_spans"] == (10 if n < 512 else 20)
+    assert 0.3 * wall < t["dp_ms"] < wall
+    assert 0 < t["prepass_ms"] < wall and 0 < t["walk_ms"] < wall
