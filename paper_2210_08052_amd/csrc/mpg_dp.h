@@ -933,32 +933,29 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
         PairState* ps = pst + item.x;
         const bool has_next = strip + 1 < nstrips;
         const int col0 = strip * LY::SW + lane * K;  // DP column of this lane's first column
-        const bool act = true;
         bool failed = false;
         uint64_t best_key = 0;
 
         // ---- strip set-up: profile, registers, first descriptors and boundary
-        if (act) {
 #pragma unroll
-            for (int c = 0; c < K; ++c) {
-                const int j = col0 + c;
-                const int pc = (j >= 1 && j <= m) ? (PRO ? 0 : aa_lds(Pa[j - 1])) : -1;
-                // all 24 entries are read before any is stored, so the reads
-                // overlap
-                int sv[24];
+        for (int c = 0; c < K; ++c) {
+            const int j = col0 + c;
+            const int pc = (j >= 1 && j <= m) ? (PRO ? 0 : aa_lds(Pa[j - 1])) : -1;
+            // all 24 entries are read before any is stored, so the reads
+            // overlap
+            int sv[24];
 #pragma unroll
-                for (int tr = 0; tr < 24; ++tr)
-                    sv[tr] = pc < 0 ? 0
-                                    : (PRO ? (int)prof_scores(Pa)[24 * (j - 1) + tr]
-                                           : (int)smat[tr * 24 + pc]);
+            for (int tr = 0; tr < 24; ++tr)
+                sv[tr] = pc < 0 ? 0
+                                : (PRO ? (int)prof_scores(Pa)[24 * (j - 1) + tr]
+                                       : (int)smat[tr * 24 + pc]);
 #pragma unroll
-                for (int tr = 0; tr < 25; ++tr) {
-                    const bool poison = pc < 0 || tr == 24;
-                    const int v = tr < 24 ? sv[tr < 24 ? tr : 0] : 0;
-                    uint8_t* at = prof + prof_offset(K, TB, tr) + lane * LY::PB + c * LY::PS;
-                    if (TB) *(int16_t*)at = (int16_t)(poison ? -32768 : 16 * v + 14);
-                    else *(int8_t*)at = (int8_t)(poison ? -128 : v);
-                }
+            for (int tr = 0; tr < 25; ++tr) {
+                const bool poison = pc < 0 || tr == 24;
+                const int v = tr < 24 ? sv[tr < 24 ? tr : 0] : 0;
+                uint8_t* at = prof + prof_offset(K, TB, tr) + lane * LY::PB + c * LY::PS;
+                if (TB) *(int16_t*)at = (int16_t)(poison ? -32768 : 16 * v + 14);
+                else *(int8_t*)at = (int8_t)(poison ? -128 : v);
             }
         }
 
@@ -981,7 +978,7 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
                 ceDv[c] = ce;
             }
         }
-        if (act) inb[lane] = make_int2(NEG, NEG);
+        inb[lane] = make_int2(NEG, NEG);
         int h1[K], h2[K], h3[K], d1[K], d2[K], d3[K], a1[K], b1[K], c1[K];
         int zl[K], best[K], bstep[K], bk[K], bkt[K], hn[K], kp[K];
         int fp[K];  // previous row's frameshift term (F1/G1 maximum)
@@ -1016,16 +1013,16 @@ dp_kernel(const PairJob* __restrict__ jobs, const int2* __restrict__ items, int 
         // registers carrying the previous two rows' donor and acceptor fields
         // (score-only: r+d(i), r+d(i-1), a(i-1), a(i-2))
         int dd0 = 0, ddm1 = 0, aam1 = 0, aam2 = 0;
-        if (act) {
+        {
             const int4 u = *(const int4*)(dsc_g + (int64_t)(-lane - 1 + kDescLo) * LY::DS);
             const int4 v = *(const int4*)(dsc_g + (int64_t)(-lane - 2 + kDescLo) * LY::DS);
             aam1 = u.w; aam2 = v.w;
-        dd0 = DDN ? vadd<F32>(u.z, kOne) : u.z;
-        ddm1 = DDN ? vadd<F32>(v.z, kTwo) : v.z;
+            dd0 = DDN ? vadd<F32>(u.z, kOne) : u.z;
+            ddm1 = DDN ? vadd<F32>(v.z, kTwo) : v.z;
         }
         // descriptor ring: rows -64..-1 then 0..63
         int4 pf0 = make_int4(0, 0, 0, 0);
-        if (act) {
+        {
             // all loads first, then the stores
             const uint8_t* src = dsc_g + (int64_t)(lane - 64 + kDescLo) * LY::DS;
             const uint8_t* src2 = dsc_g + (int64_t)(lane + kDescLo) * LY::DS;

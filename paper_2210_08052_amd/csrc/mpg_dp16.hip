@@ -167,7 +167,9 @@ __global__ void __launch_bounds__(256) prepass16_kernel(const PairJob* __restric
     }
 }
 
-// Waves per SIMD the register allocation of the int16 kernel aims at.
+// Waves per SIMD the register allocation of the int16 kernel aims at.  LDS
+// holds fewer at width 2: 16,896 B a wavefront, mostly the two pairs' score
+// tables, so nine fit a CU (2.25 per SIMD); width 1 takes 10,496 B (fifteen).
 #ifndef MPG_I16_WAVES
 #define MPG_I16_WAVES 3
 #endif

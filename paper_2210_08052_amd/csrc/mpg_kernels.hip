@@ -16,15 +16,18 @@
 //    k holding K adjacent columns.  At step s lane k computes row s-k, so the
 //    anti-diagonal order satisfies every dependency (rows i-1..i-3 of its own
 //    columns live in registers; the left neighbour's H and I of the same row
-//    arrive through a slot in LDS).  Lane 0 takes the left strip's last column
-//    from HBM, where the wavefront running the left strip publishes it 64
-//    rows at a time behind a progress counter; the kernel is persistent and
-//    takes (pair, strip) items from one queue, longest pair first;
+//    arrive through a slot in LDS, or by a DPP shift where a step has too few
+//    other instructions to cover the slot's latency).  Lane 0 takes the left
+//    strip's last column from HBM, where the wavefront running the left strip
+//    publishes it 64 rows at a time behind a progress counter; the kernel is
+//    persistent and takes (pair, strip) items from one queue, longest pair
+//    first;
 //  * traceback variant: every value is kept as 16*v + nibble, where the
 //    nibble encodes the H winner (15 - code) so one max3 chain yields the
 //    value and the first-maximum tie-break together; gap/intron extension
-//    choices are shifted into a per-lane bit register (compare + add with
-//    carry).  Both go to HBM as coalesced 256 B writes;
+//    choices, the sign bits of extension less opening, are shifted into a
+//    per-lane bit register (one funnel shift each).  Both go to HBM as
+//    coalesced 256 B writes;
 //  * walk: one wavefront per traced pair follows the stored choices back from
 //    the end cell, reading each run of the path in parallel, and writes the
 //    run-length op string.
