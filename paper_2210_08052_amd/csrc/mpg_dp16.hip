@@ -199,14 +199,13 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
     asm volatile("" : "+v"(in_off), "+v"(out_off));
     const int2* const in_l = (const int2*)(smem + in_off);
     int2* const out_l = (int2*)(smem + out_off);
-    const int most = packs[items[0].x].nchunks;
 
     for (;;) {
         const int it = __builtin_amdgcn_readfirstlane(atomicAdd(qhead, lane == 0 ? 1 : 0));
         if (it >= nitems) break;
         const int2 item = items[it];
         const PackJob X = packs[item.x];
-        strip_priority(X.nchunks, most);
+        strip_priority(X.nchunks, P.prio_chunks);
         const int strip = item.y;
         const bool hasB = X.b >= 0;
         const PairJob JA = jobs[X.a];

@@ -51,6 +51,7 @@ struct DevParams {
     // the penalties of the DP kernels' register forms, in the order of Pen:
     // pen[value form: 0 integer, 1 the bits of the fp32 number][traceback]
     int32_t pen[2][2][6];
+    int32_t prio_chunks;  // scale of a strip's issue priority (strip_priority)
 };
 // Penalties of a DP kernel: gap open (+ extend with traceback) of I and of D,
 // gap extend, frameshift, and (traceback) the frameshift less F1's and G1's

@@ -504,6 +504,7 @@ struct RunCfg {
     bool serve = false; // results pair by pair: the finishing wavefront walks
                         // the traceback and publishes the record (status
                         // last) to memory the host polls; shortest pairs first
+    bool long_lane = false;  // serving: a lane of long jobs (strips of lower priority)
     const Tuning* tune = nullptr;  // measured costs for choosing K
     bool wide = false;               // not tuned: width 2, whatever the work
     int force_K = 0, force_K16 = 0;  // calibration runs: one width for all
@@ -1150,6 +1151,10 @@ int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg,
         const int nit = (int)G.cnt;
         DevParams DG = DP;
         DG.mode = G.mode;
+        const int32_t first = P.items[G.off].x;  // in a batch the pair (or pack) with most work
+        DG.prio_chunks = cfg.serve ? (cfg.long_lane ? 1 << 30 : 0)
+                         : G.i16   ? P.packs[first].nchunks
+                                   : P.jobs[first].nchunks;
         if (G.i16)
             return launch_dp16(s2, G.K, P.fast16, cfg.ncu, DG, X.d_jobs, X.d_packs, X.d_items + X.goff[g],
                                nit, X.d_qhead + g, X.d_pst, X.d_prog, X.d_prot,
@@ -1581,7 +1586,7 @@ int align_host(hipStream_t st, Workspace& ws, const mpg_params* p, const mpg_pai
 template <typename Deliver>
 int serve_batch(hipStream_t st, Workspace& ws, const mpg_params* p, const mpg_pair* pairs,
                 int32_t n, uint64_t tb_budget, int ncu, const Tuning* tune, int force_K,
-                Deliver deliver) {
+                bool long_lane, Deliver deliver) {
     std::vector<mpg_seg> segs(n);
     int64_t pbytes = 0, dbytes = 0;
     for (int32_t k = 0; k < n; ++k) {
@@ -1623,6 +1628,7 @@ int serve_batch(hipStream_t st, Workspace& ws, const mpg_params* p, const mpg_pa
         cfg.tb_budget = tb_budget;
         cfg.ncu = ncu;
         cfg.serve = true;
+        cfg.long_lane = long_lane;
         cfg.tune = tune;
         cfg.force_K = force_K;
         return run_dev_waves(st, ws, p, d_seq, d_seq + pbytes, segs.data(), n,
@@ -1775,7 +1781,8 @@ void scheduler(mpg_ctx* c) {
         // short micro-batches always find free wavefront slots
         const int ncu = cls >= 2 ? std::max(1, (int)(g_num_cu * c->long_share)) : g_num_cu;
         const int K = cls >= 2 ? c->serve_K_long : c->serve_K_short;
-        workers[slot] = std::thread([c, slot, tb, ncu, K, params, &streams, &wss, &busy,
+        const bool long_lane = cls >= 2;
+        workers[slot] = std::thread([c, slot, tb, ncu, K, long_lane, params, &streams, &wss, &busy,
                                      b = std::move(batch)]() mutable {
             hipSetDevice(c->device);
             std::vector<mpg_pair> pairs(b.size());
@@ -1819,7 +1826,7 @@ void scheduler(mpg_ctx* c) {
                 c->cv_done.notify_all();
             };
             serve_batch(streams[slot], wss[slot], &params, pairs.data(), (int32_t)pairs.size(),
-                        (uint64_t)tb + 1, ncu, &c->tune, K, deliver);
+                        (uint64_t)tb + 1, ncu, &c->tune, K, long_lane, deliver);
             std::lock_guard<std::mutex> g(c->mu);
             c->tb_in_use -= (uint64_t)tb;
             c->stats.tb_bytes_in_use = c->tb_in_use;
