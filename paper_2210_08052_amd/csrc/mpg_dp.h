@@ -290,10 +290,11 @@ __device__ __forceinline__ uint32_t push_open(uint32_t acc, int diff) {
 
 // Issue priority of a wavefront whose strip runs `nchunks` chunks, on the scale
 // `most`: 3 from half of it on, 0 below an eighth.  In a batch `most` is that of
-// the launch's pair with most work: its longest chains go first.  Serving gives 0 to its short lanes (every
-// strip 3) and more than any strip has to its long ones (every strip 0): a
-// short job does not wait behind the long strips on its SIMD (24,000 jobs/s:
-// short jobs p99 2.8 ms, at one priority 5.8; long jobs p50 35 ms, 32).
+// the launch's pair with most work: its longest chains go first.  Serving gives
+// 0 to its short lanes (every strip 3) and more than any strip has to its long
+// ones (every strip 0): a short job does not wait behind the long strips on its
+// SIMD (24,000 jobs/s: short jobs p99 2.8 ms, at one priority 5.8; long jobs
+// p50 35 ms, 32).
 __device__ __forceinline__ void strip_priority(int nchunks, int most) {
     if (2 * nchunks >= most) __builtin_amdgcn_s_setprio(3);
     else if (4 * nchunks >= most) __builtin_amdgcn_s_setprio(2);

@@ -597,11 +597,13 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         return s.dlen >= 0 && s.plen >= 0 && s.dlen <= MPG_MAX_DNA && s.plen <= MPG_MAX_PROT &&
                b.ok(s.dlen, s.plen, pair_mode(q));
     };
+    P.ginfo.resize(cnt);
     if (by_work) {
         WidthWork ww, ww16;
         for (int32_t k = 0; k < cnt; ++k) {
             const mpg_seg& s = segs[idx[k]];
-            if (!in_range(idx[k], pair_bound(idx[k]))) continue;  // will not run
+            P.ginfo[k] = in_range(idx[k], pair_bound(idx[k]));
+            if (!P.ginfo[k]) continue;  // will not run
             const bool tb = seg_tb(s, p);
             if (allow16 && !tb && bound.ok16(s.plen, p->mode)) ww16.add16(s.dlen, s.plen);
             else ww.add(s.dlen, s.plen, tb, bound.introns);
@@ -631,7 +633,6 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
     };
     // per job: group key << 24 | traceback << 23 | strips (a compact copy for
     // the passes in queue order, which visit the jobs out of order)
-    P.ginfo.resize(cnt);
     P.seg_key.assign(cnt, -1);
     // lanes the last strip of a pair needs
     auto last_lanes = [](const PairJob& J) {
@@ -655,7 +656,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.status = MPG_OK;
         J.mode = pair_mode(idx[k]);
         const BoundInfo& bk = pair_bound(idx[k]);
-        if (!in_range(idx[k], bk)) J.status = MPG_E_RANGE;
+        if (!(by_work ? P.ginfo[k] != 0 : in_range(idx[k], bk))) J.status = MPG_E_RANGE;
         const int nn = std::max(0, J.n), mm = std::max(0, J.m);
         // a pair whose columns fit one strip of 64 takes one column per lane:
         // wider lanes would only add idle columns to every step

@@ -35,33 +35,38 @@ inline int pair_nsteps(int n, int m, int K) {
 // one of 2,000 on 8,000 1.47 and 1.32; batch recipe 1,200 pairs 3.34 and 2.43,
 // 3,000 3.54 and 4.54.
 struct WidthWork {
-    static constexpr double kStripLag = 290, kNorm = 1.3;
+    static constexpr int kStripLag = 290;
+    static constexpr double kNorm = 1.3;
     // width 1 only where it is this much faster: in doubt the wider strips,
     // whose time hangs less on where the wavefronts land
     static constexpr double kMargin = 0.97;
-    // Cycles (at 2.4 GHz) of a strip's step at width K: step + column * K.
+    // Cycles (at 2.4 GHz) of a strip's step at width K, step + column * K: on a
+    // SIMD shared by four wavefronts, and alone.
     struct Cost { double step, column; };
-    double work[2] = {0, 0}, chain[2] = {0, 0};  // [0]: width 1, [1]: width 2
-    void add(int n, int m, const Cost& shared, const Cost& alone) {
+    enum Kind { kPlain, kIntrons, kTracedPlain, kTraced, kInt16, kKinds };
+    static constexpr Cost kShared[kKinds] = {{49, 29}, {66, 45}, {56, 53}, {83, 77}, {38, 88}};
+    static constexpr Cost kAlone[kKinds] = {{94, 70}, {96, 99}, {96, 106}, {98, 174}, {74, 118}};
+    // per kind, [0]: width 1, [1]: width 2: strips x steps, and the steps of the
+    // longest chain
+    int64_t work[kKinds][2] = {}, chain[kKinds][2] = {};
+    void add(int n, int m, Kind kind) {
         for (int K = 1; K <= 2; ++K) {
-            const double steps = pair_nsteps(n, m, K);
-            const double strips = (m + 64 * K) / (64 * K);
-            work[K - 1] += (shared.step + shared.column * K) * steps * strips;
-            chain[K - 1] = std::max(chain[K - 1], (alone.step + alone.column * K) *
-                                                      (steps + kStripLag * (strips - 1)));
+            const int64_t steps = pair_nsteps(n, m, K), strips = (m + 64 * K) / (64 * K);
+            work[kind][K - 1] += steps * strips;
+            chain[kind][K - 1] = std::max(chain[kind][K - 1], steps + kStripLag * (strips - 1));
         }
     }
-    // 32-bit lanes: [traceback][introns]
-    void add(int n, int m, bool tb, bool introns) {
-        static constexpr Cost kShared[2][2] = {{{49, 29}, {66, 45}}, {{56, 53}, {83, 77}}};
-        static constexpr Cost kAlone[2][2] = {{{94, 70}, {96, 99}}, {{96, 106}, {98, 174}}};
-        add(n, m, kShared[tb][introns], kAlone[tb][introns]);
-    }
+    // 32-bit lanes
+    void add(int n, int m, bool tb, bool introns) { add(n, m, (Kind)(2 * tb + introns)); }
     // 16-bit lanes: a step advances two pairs
-    void add16(int n, int m) { add(n, m, Cost{38, 88}, Cost{74, 118}); }
+    void add16(int n, int m) { add(n, m, kInt16); }
     double time(int K, int ncu) const {
-        return std::pow(std::pow(work[K - 1] / (4.0 * ncu), kNorm) + std::pow(chain[K - 1], kNorm),
-                        1 / kNorm);
+        double w = 0, c = 0;
+        for (int k = 0; k < kKinds; ++k) {
+            w += (kShared[k].step + kShared[k].column * K) * work[k][K - 1];
+            c = std::max(c, (kAlone[k].step + kAlone[k].column * K) * chain[k][K - 1]);
+        }
+        return std::pow(std::pow(w / (4.0 * ncu), kNorm) + std::pow(c, kNorm), 1 / kNorm);
     }
     int width(int ncu) const { return time(1, ncu) < kMargin * time(2, ncu) ? 1 : 2; }
 };
