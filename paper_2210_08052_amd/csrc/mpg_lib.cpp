@@ -374,8 +374,7 @@ int g_num_cu = 256;  // compute units of the device (the DP grid is sized per CU
 
 int64_t tb_bytes_of(int n, int m, int K) {
     const int nsteps = pair_nsteps(n, m, K);
-    const int nstrips = (m + 1 + 64 * K - 1) / (64 * K);
-    return (int64_t)nstrips * (nsteps / 64) * kTbBlockBytes * K;
+    return (int64_t)pair_strips(m, K) * (nsteps / 64) * kTbBlockBytes * K;
 }
 
 // Direction-bit bytes of a pair at the width that needs most.
@@ -657,7 +656,8 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.mode = pair_mode(idx[k]);
         const BoundInfo& bk = pair_bound(idx[k]);
         if (!(by_work ? P.ginfo[k] != 0 : in_range(idx[k], bk))) J.status = MPG_E_RANGE;
-        const int nn = std::max(0, J.n), mm = std::max(0, J.m);
+        // (a refused pair's lengths may be any number)
+        const int nn = J.status == MPG_OK ? J.n : 0, mm = J.status == MPG_OK ? J.m : 0;
         // a pair whose columns fit one strip of 64 takes one column per lane:
         // wider lanes would only add idle columns to every step
         int K = (mm + 1 <= narrow && !ov.K && !cfg.force_K) ? 1 : width;
@@ -672,7 +672,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
         J.K = K;
         const int nsteps = pair_nsteps(nn, mm, K);
         J.nchunks = nsteps / 64;
-        J.nstrips = (mm + 1 + 64 * K - 1) / (64 * K);
+        J.nstrips = pair_strips(mm, K);
         J.f32 = !ov.no_f32 && bk.f32_ok(nn, mm, J.mode, J.tb != 0) ? 1 : 0;
         J.ops_off = ops_off[idx[k]];
         J.i16 = 0;
@@ -681,7 +681,7 @@ void plan_pairs(const mpg_params* p, const mpg_seg* segs, const int32_t* idx, in
             J.i16 = 1;
             J.K = K16;
             P.fast16 = P.fast16 && bound.fast16(mm);
-            J.nstrips = (mm + 1 + 64 * K16 - 1) / (64 * K16);
+            J.nstrips = pair_strips(mm, K16);
             J.nchunks = pair_nsteps(nn, mm, K16) / 64;
             // pairs are matched by shape: strips first, then chunks
             e16.push_back({(int64_t)J.nstrips * (1LL << 32) + J.nchunks, k});

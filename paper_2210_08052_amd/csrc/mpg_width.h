@@ -8,13 +8,17 @@
 
 namespace mpg {
 
+// Strips of a pair of m residues (columns 0..m) at K = 1, 2 or 4 columns per
+// lane.  (K >> 1 is K's logarithm: a call plans up to 10^5 pairs, and a division
+// by a variable costs more than the rest.)
+inline int pair_strips(int m, int K) { return (m + 64 * K) >> (6 + (K >> 1)); }
+
 // Steps every strip of a pair runs (a multiple of 64).  Lane L reaches row
 // n at step n + L: a pair of one strip stops once the lane of column m has,
 // the strips of a wider pair run all 64 lanes to row n.
 inline int pair_nsteps(int n, int m, int K) {
-    const int nstrips = (m + 1 + 64 * K - 1) / (64 * K);
-    const int lanes = nstrips == 1 ? m / K + 1 : 64;
-    return ((n + lanes + 63) / 64) * 64;
+    const int lanes = pair_strips(m, K) == 1 ? (m >> (K >> 1)) + 1 : 64;
+    return (n + lanes + 63) & ~63;
 }
 
 // Width 1 or 2 for a call, from what bounds it: its work (strips x steps)
@@ -51,7 +55,7 @@ struct WidthWork {
     int64_t work[kKinds][2] = {}, chain[kKinds][2] = {};
     void add(int n, int m, Kind kind) {
         for (int K = 1; K <= 2; ++K) {
-            const int64_t steps = pair_nsteps(n, m, K), strips = (m + 64 * K) / (64 * K);
+            const int64_t steps = pair_nsteps(n, m, K), strips = pair_strips(m, K);
             work[kind][K - 1] += steps * strips;
             chain[kind][K - 1] = std::max(chain[kind][K - 1], steps + kStripLag * (strips - 1));
         }
