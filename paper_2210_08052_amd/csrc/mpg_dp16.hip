@@ -200,12 +200,15 @@ dp16_kernel(const PairJob* __restrict__ jobs, const PackJob* __restrict__ packs,
     const int2* const in_l = (const int2*)(smem + in_off);
     int2* const out_l = (int2*)(smem + out_off);
 
+    // (the host's scale for batches too costs 1%: 4,000 pairs 5.16 -> 5.22 ms)
+    const int most = P.prio_chunks < 0 ? packs[items[0].x].nchunks : P.prio_chunks;
+
     for (;;) {
         const int it = __builtin_amdgcn_readfirstlane(atomicAdd(qhead, lane == 0 ? 1 : 0));
         if (it >= nitems) break;
         const int2 item = items[it];
         const PackJob X = packs[item.x];
-        strip_priority(X.nchunks, P.prio_chunks);
+        strip_priority(X.nchunks, most);
         const int strip = item.y;
         const bool hasB = X.b >= 0;
         const PairJob JA = jobs[X.a];

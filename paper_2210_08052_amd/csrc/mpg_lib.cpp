@@ -1152,10 +1152,11 @@ int enqueue(hipStream_t st, Workspace& ws, const Prepared& X, const RunCfg& cfg,
         const int nit = (int)G.cnt;
         DevParams DG = DP;
         DG.mode = G.mode;
-        const int32_t first = P.items[G.off].x;  // in a batch the pair (or pack) with most work
+        // in a batch the first item is of the pair with most work (the int16
+        // kernel reads its own)
         DG.prio_chunks = cfg.serve ? (cfg.long_lane ? 1 << 30 : 0)
-                         : G.i16   ? P.packs[first].nchunks
-                                   : P.jobs[first].nchunks;
+                         : G.i16   ? -1
+                                   : P.jobs[P.items[G.off].x].nchunks;
         if (G.i16)
             return launch_dp16(s2, G.K, P.fast16, cfg.ncu, DG, X.d_jobs, X.d_packs, X.d_items + X.goff[g],
                                nit, X.d_qhead + g, X.d_pst, X.d_prog, X.d_prot,
